@@ -31,6 +31,7 @@ constexpr int kMaxStepsPerSplit = 1 << 17;
 // threads per 64 QT rows, and a grid's x extent in threads must stay below
 // 2^32 (QT >= 1).
 constexpr int64_t kMaxRows = int64_t(1) << 30;
+constexpr int kSlotWords = 64;           // words of a plan's slots (one alignment unit)
 constexpr int kDefaultSlots = 512;       // resident workgroups assumed when no device can be queried
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -374,7 +375,7 @@ struct Plan {
   int64_t G = 1;               // problems sharing each launch (split counts are chosen for G)
   int64_t Mp = 0, Np = 0;
   bool alias = false;          // q and k are the same array
-  uint32_t* slots = nullptr;   // [0] |v| max, [1] |dout| max, [2] |q| max, [3] |k| max
+  uint32_t* slots = nullptr;   // [0] |v| max, [1] |dout| max, [2] |q| max, [3] |k| max; kSlotWords words
   Side q, k;
   Vals v, g;
   float* scal_kv = nullptr;    // per-step scalars, keys k with values v
@@ -488,18 +489,6 @@ DqK dq_for(const gs_problem& p, const Dims& dm, bool fused) {
 const void* fwd_kernel(const gs_problem& p, const Dims& dm) { return fwd_for(p, dm).kernel; }
 const void* dq_kernel(const gs_problem& p, const Dims& dm, bool fused) { return dq_for(p, dm, fused).kernel; }
 
-// Small forward problems: the preparation in one launch (k_prep_fwd_small)
-// and a row check that reads its key sample from the key copy, instead of
-// nine dependent launches.  Bounds: every workgroup of the preparation
-// reduces all N C values itself, and the point copies stay small.
-constexpr int64_t kSmallValues = 8192;        // N * C
-constexpr int64_t kSmallPointHalves = 1 << 18; // padded rows x RT width, per point set
-
-bool small_forward(const gs_problem& p, const Want& w, const Plan& pl, int64_t G) {
-  return w.fwd && !w.dq && !w.dk && !w.dv && G == 1 && p.N * p.C <= kSmallValues &&
-         pl.Mp * pl.dm.W() <= kSmallPointHalves && pl.Np * pl.dm.W() <= kSmallPointHalves;
-}
-
 // Lays out every buffer the requested passes need for one problem of a group
 // of G; with ws == nullptr only computes the size.
 void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& pl, int64_t G) {
@@ -511,7 +500,7 @@ void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& p
   const int W = pl.dm.W(), Wv = pl.dm.Wv(), Rv = pl.dm.Rv();
   Carver cv;
   cv.base = static_cast<char*>(ws);
-  pl.slots = cv.take<uint32_t>(64);
+  pl.slots = cv.take<uint32_t>(kSlotWords * 4);
   if (p.qk_dtype == GS_F32) {
     // fp32 tier (forward): split copies, half norms, step scalars, and for
     // several channels the split values (KS layout)
@@ -633,8 +622,6 @@ void prof_release() {
 inline unsigned grid1(int64_t n, int threads = 256) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, threads), 1 << 20));
 }
-// Reductions: at most 512 workgroups (grid-stride), one atomic each.
-inline unsigned grid_reduce(int64_t n) { return std::min(grid1(n), 128u); }
 
 // A launch group: G problems on grid.z, each with a workspace slice of
 // `slice` bytes (pl describes the first one).
@@ -654,157 +641,186 @@ inline Bz bz_ws(const Ctx& c) {
 }
 inline dim3 grid_g(const Ctx& c, unsigned x, unsigned y = 1) { return dim3(x, y, c.G); }
 
-// xs: byte stride of x between problems.  sgn / sgn_dt / sgns: for
-// single-channel problems, the values whose signs the KS copy of these points
-// (as keys of a gradient pass) carries, and their stride; else NULL.
-template <typename T>
-void prep_points_t(const Ctx& c, const uint16_t* x16, int64_t xs, int64_t n, int64_t n_pad, Side& s,
-                   uint32_t* slot, const void* sgn, int sgn_dt, int64_t sgns) {
-  const gs_problem& p = *c.p;
-  const int W = c.pl->dm.W();
-  Bz bz = bz_ws(c);
-  bz.in = xs;
-  bz.in2 = sgns;
-  // 16-byte row loads when every problem's rows start on 16-byte boundaries
-  const int vec = (p.D % 8 == 0) && ((reinterpret_cast<uintptr_t>(x16) | (uintptr_t)xs) % 16 == 0);
-  hipLaunchKernelGGL(k_points_rt_norm<T>, grid_g(c, grid1(n_pad * (W / 8))), dim3(256), 0, c.st, x16, n,
-                     (int)p.D, n_pad, W, s.rt, s.nh, vec, bz);
-  if (s.samp_rt)
-    hipLaunchKernelGGL(k_sample, grid_g(c, grid1(kSampleRows * W)), dim3(256), 0, c.st, x16, n, (int)p.D,
-                       W, (const float*)s.nh, s.samp_rt, s.samp_nh, bz);
-  if (s.ks) {
-    const uint32_t* sl = nullptr;
-    if (p.qk_dtype == GS_BF16) {
-      hipLaunchKernelGGL(k_absmax, grid_g(c, grid_reduce(n * p.D)), dim3(256), 0, c.st,
-                         static_cast<const void*>(x16), n * p.D, 2, slot, bz);
-      sl = slot;
+// ------------------------------------------------------------ preparation
+
+// Maxima are taken by every workgroup of k_prep itself when all arrays hold
+// at most this many elements together (a few loads per thread, against a
+// launch of its own for k_prep_max: 3 - 4 us).
+constexpr int64_t kInlineMaxElements = 16384;
+// ... and the launch has at most this many workgroups (each repeats it).
+constexpr int64_t kInlineMaxBlocks = 1024;
+// Workgroups of a k_prep launch: one item per thread up to this many, then
+// more items per thread.
+constexpr int64_t kPrepBlocks = 4096;
+// Partial maxima per array of k_prep_max: they lie where the row check later
+// puts its flags (at least kRowPad words, free until then), the fp32 tier's
+// in the unused words of the slots.
+constexpr int kMaxParts = kRowPad / kMaxSlots;
+constexpr int kMaxParts32 = 16, kPartWord32 = 16;
+static_assert(kPartWord32 + 3 * kMaxParts32 <= kSlotWords, "partial maxima of v, q and k behind the slots");
+
+// The words of the row-check flags of some key side of this plan.
+inline uint32_t* row_flag_words(const Plan& pl) {
+  float* nh = pl.k.samp_nh ? pl.k.samp_nh : pl.q.samp_nh;
+  return reinterpret_cast<uint32_t*>(nh + kSampleRows);
+}
+
+inline int log2i(int64_t x) {
+  int l = 0;
+  while (((int64_t)1 << (l + 1)) <= x) ++l;
+  return l;
+}
+
+// Collects the arrays to prepare, then launches k_prep (and k_prep_max).
+struct Prep {
+  const Ctx& c;
+  PrepArgs a{};
+  int64_t max_elements = 0;
+
+  explicit Prep(const Ctx& ctx) : c(ctx) {
+    a.tau2 = ctx.tau2;
+    a.slots = ctx.pl->slots;
+  }
+  // The largest magnitude of `count` elements of x goes to `slot`.
+  void maximum(int slot, const void* x, int dt, int64_t bz, int64_t count) {
+    for (int i = 0; i < a.nmax; ++i)
+      if (a.mx[i].slot == slot) return;
+    a.mx[a.nmax++] = MaxSource{x, bz, count, dt, slot, 0};
+    max_elements += count;
+  }
+  PrepJob& add(int kind, const void* src, int64_t bz, int64_t n, int64_t items, int width, int lg, uint16_t* out) {
+    PrepJob& j = a.job[a.jobs++];
+    j.kind = kind;
+    j.width = width;
+    j.lg = lg;
+    j.slot = -1;
+    j.n = n;
+    j.items = items;
+    j.src = src;
+    j.bz = bz;
+    j.out = out;
+    return j;
+  }
+  int vec(const void* x, int64_t bz) const {
+    return (c.p->D % 8 == 0) && ((reinterpret_cast<uintptr_t>(x) | (uintptr_t)bz) % 16 == 0);
+  }
+
+  // Points: RT copy, half norms, sample, and the key scalars k0 / k1.
+  void points(const void* x, int64_t bz, int64_t n, int64_t n_pad, const Side& s, KeyScalars k0, KeyScalars k1) {
+    const int W = c.pl->dm.W(), lg = log2i(W / 8), D = (int)c.p->D;
+    PrepJob& j = add(kJobPoints, x, bz, n, n_pad << lg, D, lg, s.rt);
+    j.vec = vec(x, bz);
+    j.nh = s.nh;
+    j.ks[0] = k0;
+    j.ks[1] = k1;
+    if (s.samp_rt) {
+      PrepJob& m = add(kJobSample, x, bz, n, (int64_t)kSampleRows << lg, D, lg, s.samp_rt);
+      m.vec = vec(x, bz);
+      m.nh = s.samp_nh;
     }
-    hipLaunchKernelGGL(k_points_ks<T>, grid_g(c, grid1(n_pad / 8 * W)), dim3(256), 0, c.st, x16, n,
-                       (int)p.D, n_pad, W, sl, sgn, (int)sgn_dt, s.ks, bz);
   }
-}
-
-void prep_points(const Ctx& c, const void* x, int64_t xs, int64_t n, int64_t n_pad, Side& s,
-                 uint32_t* slot, const void* sgn = nullptr, int sgn_dt = GS_F32, int64_t sgns = 0) {
-  const uint16_t* x16 = static_cast<const uint16_t*>(x);
-  if (c.p->qk_dtype == GS_F16)
-    prep_points_t<F16>(c, x16, xs, n, n_pad, s, slot, sgn, sgn_dt, sgns);
-  else
-    prep_points_t<BF16>(c, x16, xs, n, n_pad, s, slot, sgn, sgn_dt, sgns);
-}
-
-// KS copy only (the second, differently signed copy of aliased points).
-void prep_points_ks(const Ctx& c, const void* x, int64_t xs, int64_t n, int64_t n_pad, uint16_t* ks,
-                    uint32_t* slot, const void* sgn, int sgn_dt, int64_t sgns) {
-  const gs_problem& p = *c.p;
-  const int W = c.pl->dm.W();
-  const uint16_t* x16 = static_cast<const uint16_t*>(x);
-  const uint32_t* sl = p.qk_dtype == GS_BF16 ? slot : nullptr;
-  Bz bz = bz_ws(c);
-  bz.in = xs;
-  bz.in2 = sgns;
-  if (p.qk_dtype == GS_F16)
-    hipLaunchKernelGGL(k_points_ks<F16>, grid_g(c, grid1(n_pad / 8 * W)), dim3(256), 0, c.st, x16, n,
-                       (int)p.D, n_pad, W, sl, sgn, (int)sgn_dt, ks, bz);
-  else
-    hipLaunchKernelGGL(k_points_ks<BF16>, grid_g(c, grid1(n_pad / 8 * W)), dim3(256), 0, c.st, x16, n,
-                       (int)p.D, n_pad, W, sl, sgn, (int)sgn_dt, ks, bz);
-}
-
-void prep_values(const Ctx& c, const void* x, int dt, int64_t xs, int64_t n, int64_t n_pad,
-                 Vals& s, uint32_t* slot) {
-  const gs_problem& p = *c.p;
-  const int Wv = c.pl->dm.Wv(), Rv = c.pl->dm.Rv();
-  Bz bz = bz_ws(c);
-  bz.in = xs;
-  if (n > 0)
-    hipLaunchKernelGGL(k_absmax, grid_g(c, grid_reduce(n * p.C)), dim3(256), 0, c.st, x, n * p.C, (int)dt,
-                       slot, bz);
-  if (s.rt)
-    hipLaunchKernelGGL(k_values_rt, grid_g(c, grid1(n_pad * Wv)), dim3(256), 0, c.st, x, (int)dt, n,
-                       (int)p.C, n_pad, Wv, (const uint32_t*)slot, s.rt, bz);
-  if (s.ks)
-    hipLaunchKernelGGL(k_values_ks, grid_g(c, grid1(n_pad / 8 * Rv)), dim3(256), 0, c.st, x, (int)dt, n,
-                       (int)p.C, n_pad, Rv, (const uint32_t*)slot, (int)(p.C == 1), s.ks, bz);
-}
-
-// Per-step key scalars of key side `s` paired with values x (byte stride xs,
-// slot = their absolute maximum): single-channel problems fold log2|v| and
-// sign(v) in, otherwise half norms only.
-void prep_scalars(const Ctx& c, const Side& s, const void* x, int dt, int64_t xs, int64_t n,
-                  int64_t n_pad, const uint32_t* slot, float* out) {
-  const bool vals = c.p->C == 1 && x != nullptr;
-  Bz bz = bz_ws(c);
-  bz.in = vals ? xs : 0;
-  hipLaunchKernelGGL(k_step_scalars, grid_g(c, grid1(n_pad * 2)), dim3(256), 0, c.st, (const float*)s.nh,
-                     vals ? x : nullptr, (int)dt, n, n_pad, slot, c.tau2, out, bz);
-}
-
-// Row-bound flags of the rows of `qs` (n rows, n_pad padded) against the
-// sampled keys of `ks`, stored after the sample's half norms.
-template <typename T, bool GATHER>
-void row_check_t(const Ctx& c, const Side& qs, int64_t n, int64_t n_pad, const Side& ks, int64_t nk) {
-  uint32_t* shift = reinterpret_cast<uint32_t*>(ks.samp_nh + kSampleRows);
-  const dim3 grid = grid_g(c, (unsigned)(n_pad / 256)), block(kBlockThreads);
-  const uint4* q = (const uint4*)qs.rt;
-  // the copied sample, or (GATHER) the key set's own RT copy and half norms
-  const uint4* s = (const uint4*)(GATHER ? ks.rt : ks.samp_rt);
-  const float* snh = GATHER ? ks.nh : ks.samp_nh;
-  const Bz bz = bz_ws(c);
-  switch (c.pl->dm.DP) {
-    case 1: hipLaunchKernelGGL((k_row_check<T, 1, GATHER>), grid, block, 0, c.st, q, qs.nh, s, snh, c.tau2, n, shift, bz, nk); break;
-    case 2: hipLaunchKernelGGL((k_row_check<T, 2, GATHER>), grid, block, 0, c.st, q, qs.nh, s, snh, c.tau2, n, shift, bz, nk); break;
-    case 4: hipLaunchKernelGGL((k_row_check<T, 4, GATHER>), grid, block, 0, c.st, q, qs.nh, s, snh, c.tau2, n, shift, bz, nk); break;
-    case 8: hipLaunchKernelGGL((k_row_check<T, 8, GATHER>), grid, block, 0, c.st, q, qs.nh, s, snh, c.tau2, n, shift, bz, nk); break;
+  // KS copy of points, scaled by the maximum `slot` for bf16, with the signs
+  // of sgn.val (single channel).
+  void points_ks(const void* x, int64_t bz, int64_t n, int64_t n_pad, uint16_t* ks, int slot, KeyScalars sgn) {
+    const int W = c.pl->dm.W();
+    PrepJob& j = add(kJobPointsKs, x, bz, n, n_pad / 8 * W, (int)c.p->D, log2i(W), ks);
+    if (c.p->qk_dtype == GS_BF16) {
+      j.slot = slot;
+      maximum(slot, x, GS_BF16, bz, n * c.p->D);
+    }
+    j.ks[0] = sgn;
   }
-}
+  void values(const void* v, int dt, int64_t bz, int64_t n, int64_t n_pad, int C, const Vals& s, int slot) {
+    if (s.rt) {
+      const int lg = log2i(c.pl->dm.Wv() / 8);
+      PrepJob& j = add(kJobValuesRt, v, bz, n, n_pad << lg, C, lg, s.rt);
+      j.dtype = dt;
+      j.slot = slot;
+    }
+    if (s.ks) values_ks(v, dt, bz, n, n_pad, C, c.pl->dm.Rv(), s.ks, slot, C == 1);
+  }
+  void values_ks(const void* v, int dt, int64_t bz, int64_t n, int64_t n_pad, int C, int R, uint16_t* ks, int slot,
+                 bool signs) {
+    PrepJob& j = add(kJobValuesKs, v, bz, n, n_pad / 8 * R, C, log2i(R), ks);
+    j.dtype = dt;
+    j.slot = slot;
+    j.flag = signs;
+  }
 
-// Row-bound flags of the rows of qs against the key sample of ks; gather:
-// read the sampled keys from ks's own RT copy (nk keys) instead of a copy.
-void row_check(const Ctx& c, const Side& qs, int64_t n, int64_t n_pad, const Side& ks, bool gather = false,
-               int64_t nk = 0) {
-  if (c.p->qk_dtype == GS_F16) {
-    if (gather)
-      row_check_t<F16, true>(c, qs, n, n_pad, ks, nk);
+  // part: room for `pitch` partial maxima of each array.
+  void launch(uint32_t* part, int pitch) {
+    const Bz bz = bz_ws(c);
+    a.part = part;
+    a.pitch = pitch;
+    int64_t total = 0;
+    for (int i = 0; i < a.jobs; ++i) total += ceil_div(a.job[i].items, 256);
+    const int64_t per = ceil_div(total * c.G, kPrepBlocks);  // items per thread
+    unsigned blocks = 0;
+    for (int i = 0; i < kMaxJobs + 1; ++i) {
+      a.first[i] = blocks;
+      if (i < a.jobs) blocks += (unsigned)ceil_div(a.job[i].items, 256 * per);
+    }
+    if (a.nmax > 0 && (max_elements > kInlineMaxElements || (int64_t)blocks * c.G > kInlineMaxBlocks)) {
+      MaxArgs m{};
+      m.n = a.nmax;
+      int most = 1;
+      for (int i = 0; i < a.nmax; ++i) {
+        // 8192 elements per workgroup and round
+        a.mx[i].parts = (int)std::min<int64_t>(pitch, std::max<int64_t>(1, ceil_div(a.mx[i].count, 8 * kMaxBlock)));
+        m.src[i] = a.mx[i];
+        most = std::max(most, a.mx[i].parts);
+      }
+      hipLaunchKernelGGL(k_prep_max, grid_g(c, (unsigned)most, (unsigned)a.nmax), dim3(kMaxBlock), 0, c.st, m, part,
+                         pitch, bz);
+    }
+    const dim3 grid = grid_g(c, blocks), block(256);
+    if (c.p->qk_dtype == GS_F32)
+      hipLaunchKernelGGL((k_prep<F16, true>), grid, block, 0, c.st, a, bz);
+    else if (c.p->qk_dtype == GS_F16)
+      hipLaunchKernelGGL((k_prep<F16, false>), grid, block, 0, c.st, a, bz);
     else
-      row_check_t<F16, false>(c, qs, n, n_pad, ks, nk);
-  } else {
-    if (gather)
-      row_check_t<BF16, true>(c, qs, n, n_pad, ks, nk);
-    else
-      row_check_t<BF16, false>(c, qs, n, n_pad, ks, nk);
+      hipLaunchKernelGGL((k_prep<BF16, false>), grid, block, 0, c.st, a, bz);
   }
-}
+};
 
-void prep_fwd_small(const Ctx& c, const void* q, const void* k, const void* v, bool alias) {
-  const gs_problem& p = *c.p;
-  Plan& pl = *c.pl;
-  const int W = pl.dm.W(), R = pl.dm.Rv();
-  const int64_t items = pl.Mp * (W / 8) + (alias ? 0 : pl.Np * (W / 8)) + (pl.Np / 32) * R * 4 + pl.Np;
-  const unsigned blocks = (unsigned)std::min<int64_t>(ceil_div(items, 256), 1024);
-  auto vec = [&](const void* x) {
-    return (int)((p.D % 8 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0));
+// Rows x of one direction of a row check: n rows of qs (n_pad padded) against
+// the sampled keys of ks.
+struct CheckRows {
+  const Side* qs = nullptr;
+  int64_t n = 0, n_pad = 0;
+  const Side* ks = nullptr;
+};
+
+// Row-bound flags of one or two directions, stored after the samples' half norms.
+void row_check(const Ctx& c, const CheckRows& x, const CheckRows& y = CheckRows()) {
+  auto side = [](const CheckRows& r) {
+    return r.qs ? CheckSide{(const uint4*)r.qs->rt, r.qs->nh, (const uint4*)r.ks->samp_rt, r.ks->samp_nh, r.n}
+                : CheckSide{};
   };
-  const uint16_t* q16 = static_cast<const uint16_t*>(q);
-  const uint16_t* k16 = static_cast<const uint16_t*>(k);
-  if (p.qk_dtype == GS_F16)
-    hipLaunchKernelGGL(k_prep_fwd_small<F16>, dim3(blocks), dim3(256), 0, c.st, q16, k16, (int)alias, v,
-                       (int)p.v_dtype, p.M, p.N, (int)p.D, (int)p.C, pl.Mp, pl.Np, W, R, vec(q), vec(k), c.tau2,
-                       pl.q.rt, pl.q.nh, pl.k.rt, pl.k.nh, pl.v.ks, pl.scal_kv, pl.slots);
-  else
-    hipLaunchKernelGGL(k_prep_fwd_small<BF16>, dim3(blocks), dim3(256), 0, c.st, q16, k16, (int)alias, v,
-                       (int)p.v_dtype, p.M, p.N, (int)p.D, (int)p.C, pl.Mp, pl.Np, W, R, vec(q), vec(k), c.tau2,
-                       pl.q.rt, pl.q.nh, pl.k.rt, pl.k.nh, pl.v.ks, pl.scal_kv, pl.slots);
+  const unsigned b0 = (unsigned)(x.n_pad / 256), b1 = (unsigned)(y.n_pad / 256);
+  const CheckSide a = side(x), b = side(y);
+  const dim3 grid = grid_g(c, b0 + b1), block(kBlockThreads);
+  const Bz bz = bz_ws(c);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, c.st, a, b, b0, c.tau2, bz); };
+  const bool f16 = c.p->qk_dtype == GS_F16;
+  switch (c.pl->dm.DP) {
+    case 1: f16 ? go(k_row_check<F16, 1>) : go(k_row_check<BF16, 1>); break;
+    case 2: f16 ? go(k_row_check<F16, 2>) : go(k_row_check<BF16, 2>); break;
+    case 4: f16 ? go(k_row_check<F16, 4>) : go(k_row_check<BF16, 4>); break;
+    case 8: f16 ? go(k_row_check<F16, 8>) : go(k_row_check<BF16, 8>); break;
+  }
 }
 
 // Split partials (in the workspace slices) -> out (byte stride out_stride).
+// A second output of the same pass (part1, count1 > 0) goes into the same launch.
 void combine(const Ctx& c, const PassShape& ps, const float* part, int64_t count, float* out,
-             int64_t out_stride) {
+             int64_t out_stride, const float* part1 = nullptr, int64_t count1 = 0, float* out1 = nullptr,
+             int64_t out1_stride = 0) {
   if (ps.splits <= 1) return;
-  Bz bz = bz_ws(c);
-  bz.out = out_stride;
-  hipLaunchKernelGGL(k_combine, grid_g(c, grid1(count)), dim3(256), 0, c.st, part, ps.splits, count, out,
-                     bz);
+  auto blocks = [](int64_t n) { return n ? grid1(n % 4 ? n : n / 4) : 0u; };
+  const unsigned b0 = blocks(count), b1 = blocks(count1);
+  hipLaunchKernelGGL(k_combine, grid_g(c, b0 + b1), dim3(256), 0, c.st, CombineSeg{part, out, count, out_stride},
+                     CombineSeg{part1, out1, count1, out1_stride}, b0, ps.splits, bz_ws(c));
 }
 
 // Forward-type pass: out[m, :] = sum_n Phi(x_m, y_n) val_n for x = qside rows
@@ -856,8 +872,7 @@ void pass_dq(const Ctx& c, const Side& qs, int64_t nq, const Side& ks, int64_t n
             g1, (int)g1_dt, c.tau2, c.tau, nq, (int)p.D, ps.steps, ps.sps, dst, split ? nq * p.D : 0,
             (const uint4*)vks, (int)p.C, dst_s, split ? nq * p.C : 0, bz);
   prof_after(kKindGrad, c.st);
-  combine(c, ps, c.pl->part, nq * p.D, out, os);
-  if (fused) combine(c, ps, c.pl->part_s, nq * p.C, out_s, os_s);
+  combine(c, ps, c.pl->part, nq * p.D, out, os, c.pl->part_s, fused ? nq * p.C : 0, out_s, os_s);
 }
 
 // fp32 tier: prep (maxima, split copies, step scalars) and the forward pass
@@ -868,34 +883,31 @@ void run_f32(const Ctx& c, const void* q, int64_t qs, const void* k, int64_t ks,
   Plan& pl = *c.pl;
   const int W = pl.dm.W(), DP = pl.dm.DP;
   const int64_t M = p.M, N = p.N;
-  Bz bz = bz_ws(c);
-  hipLaunchKernelGGL(k_fill_u32, grid_g(c, 1), dim3(64), 0, c.st, pl.slots, 16, 0u, bz);
-  auto points = [&](const void* x, int64_t xs, int64_t n, int64_t n_pad, Side& sd, uint32_t* slot) {
-    Bz b = bz_ws(c);
-    b.in = xs;
-    hipLaunchKernelGGL(k_absmax, grid_g(c, grid_reduce(n * p.D)), dim3(256), 0, c.st, x, n * p.D, 0, slot, b);
-    hipLaunchKernelGGL(k_points_split, grid_g(c, grid1(n_pad * (W / 8))), dim3(256), 0, c.st,
-                       static_cast<const float*>(x), n, (int)p.D, n_pad, W, (const uint32_t*)slot, sd.rt,
-                       sd.lo, sd.nh, b);
-  };
-  points(q, qs, M, pl.Mp, pl.q, pl.slots + 2);
-  if (!pl.alias) points(k, ks, N, pl.Np, pl.k, pl.slots + 3);
-  const int kslot = pl.alias ? 2 : 3;
-  Bz bv = bz_ws(c);
-  bv.in = vst;
   const int64_t C = p.C;
-  hipLaunchKernelGGL(k_absmax, grid_g(c, grid_reduce(N * C)), dim3(256), 0, c.st, v, N * C, (int)p.v_dtype,
-                     pl.slots + 0, bv);
+  const int kslot = pl.alias ? 2 : 3;
+  Prep prep(c);
+  const int lg = log2i(W / 8);
+  const KeyScalars keys{pl.scal_kv, C == 1 ? v : nullptr, vst, (int)p.v_dtype, 0};
+  auto points = [&](const void* x, int64_t xs, int64_t n, int64_t n_pad, const Side& sd, int slot, bool is_keys) {
+    prep.maximum(slot, x, GS_F32, xs, n * p.D);
+    PrepJob& j = prep.add(kJobSplit, x, xs, n, n_pad << lg, (int)p.D, lg, sd.rt);
+    j.out2 = sd.lo;
+    j.nh = sd.nh;
+    j.slot = slot;
+    if (is_keys) j.ks[0] = keys;
+  };
+  prep.a.qslot = 2;
+  prep.a.kslot = kslot;
+  prep.maximum(0, v, p.v_dtype, vst, N * C);
+  points(q, qs, M, pl.Mp, pl.q, 2, pl.alias);
+  if (!pl.alias) points(k, ks, N, pl.Np, pl.k, 3, true);
   if (C > 1) {
-    const int Rv = pl.dm.Rv();
-    hipLaunchKernelGGL(k_values_ks_split, grid_g(c, grid1(pl.Np / 8 * Rv)), dim3(256), 0, c.st, v,
-                       (int)p.v_dtype, N, (int)C, pl.Np, Rv, (const uint32_t*)pl.slots + 0, pl.v.ks, pl.v.rt,
-                       bv);
+    PrepJob& j = prep.add(kJobValuesKsSplit, v, vst, N, pl.Np / 8 * pl.dm.Rv(), (int)C, log2i(pl.dm.Rv()), pl.v.ks);
+    j.out2 = pl.v.rt;
+    j.dtype = p.v_dtype;
+    j.slot = 0;
   }
-  hipLaunchKernelGGL(k_step_scalars32, grid_g(c, grid1(pl.Np * 2)), dim3(256), 0, c.st,
-                     (const float*)pl.k.nh, C == 1 ? v : nullptr, (int)p.v_dtype, N, pl.Np,
-                     (const uint32_t*)pl.slots + 0, (const uint32_t*)pl.slots + 2,
-                     (const uint32_t*)pl.slots + kslot, c.tau2, pl.scal_kv, bv);
+  prep.launch(pl.slots + kPartWord32, kMaxParts32);
   if (C > 1) {
     // several channels: launches of up to kF32MaxChannels channels each
     const int CT = f32c_ct(C);
@@ -1002,13 +1014,15 @@ using namespace gs;
 
 namespace {
 constexpr int kDotBlocks = 256;
+// Elements one workgroup of k_dot sums alone (16 per thread): below that a
+// second launch to add the partials costs more than it saves.
+constexpr int64_t kDotOneBlock = 16 * kDotThreads;
 
-// Leading workspace of gauss_sum_mmd_flow: all-ones upstream gradient (n
-// fp32), the forward sum when the caller does not want it (n fp32), the
-// reduction partials; the gradient pass's own workspace follows.
+// Leading workspace of gauss_sum_mmd_flow: the forward sum when the caller
+// does not want it (n fp32), the reduction partials; the gradient pass's own
+// workspace follows.
 size_t flow_extra(int64_t n) {
-  const int64_t a = gs::round_up(std::max<int64_t>(n, 1) * 4, 256);
-  return (size_t)(2 * a + gs::round_up(kDotBlocks * 8, 256));
+  return (size_t)(gs::round_up(std::max<int64_t>(n, 1) * 4, 256) + gs::round_up(kDotBlocks * 8, 256));
 }
 }  // namespace
 
@@ -1149,10 +1163,12 @@ int64_t group_size(const gs_problem& p, const Want& w, bool alias, int64_t cnt, 
 // workspace) before anything is enqueued, then runs the problems in launch
 // groups: prep kernels and passes for the requested outputs (out: forward
 // sum, dq / dk / dv: gradients; NULL = not requested), each launch covering a
-// whole group on grid.z.
+// whole group on grid.z.  unit_dout: an upstream gradient of ones (single
+// channel, dq only; dout is then NULL).
 gs_status run(const gs_problem* p, const gs_batch* b, const void* q, const void* k, const void* v,
               float tau, const void* dout, int dout_dtype, float* out, float* dq, float* dk,
-              float* dv, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+              float* dv, void* workspace, size_t workspace_bytes, hipStream_t stream,
+              bool unit_dout = false) {
   gs_status st = check_problem(p);
   if (st != GS_SUCCESS) return st;
   if ((st = check_tau(tau)) != GS_SUCCESS) return st;
@@ -1176,7 +1192,7 @@ gs_status run(const gs_problem* p, const gs_batch* b, const void* q, const void*
   if (cnt > 1 && ((out && bt.out_stride < M * C) || (dq && bt.dq_stride < M * D) ||
                   (dk && bt.dk_stride < N * D) || (dv && bt.dv_stride < N * C)))
     return GS_ERR_BAD_SHAPE;
-  if ((M > 0 && (!q || (grads && !dout))) || (N > 0 && (!k || !v))) return GS_ERR_NULL_POINTER;
+  if ((M > 0 && (!q || (grads && !dout && !unit_dout))) || (N > 0 && (!k || !v))) return GS_ERR_NULL_POINTER;
   const int64_t vs = (int64_t)dsize(p->v_dtype), gsz = (int64_t)dsize(dout_dtype);
   // (strides count elements, so every problem's pointers keep the alignment
   // of the first one's)
@@ -1266,35 +1282,31 @@ gs_status run(const gs_problem* p, const gs_batch* b, const void* q, const void*
       run_f32(c, q_, qs, k_, ks, v_, vst, out_, os);
       continue;
     }
-    if (small_forward(*p, w, pl, G)) {
-      prep_fwd_small(c, q_, k_, v_, alias);
-      row_check(c, pl.q, M, pl.Mp, pl.k, true, N);
-      pass_fwd(c, pl.q, M, pl.k, N, pl.scal_kv, pl.v.ks, pl.slots + 0, out_, os);
-      continue;
-    }
-    hipLaunchKernelGGL(k_fill_u32, grid_g(c, 1), dim3(64), 0, stream, pl.slots, 16, 0u, bz_ws(c));
-    if (alias) {
-      // q.ks serves dk (keys q, signs of dout) unless only dq wants a KS copy
-      const bool q_for_dk = w.dk;
-      prep_points(c, q_, qs, M, pl.Mp, pl.q, pl.slots + 2, one_c ? (q_for_dk ? g_ : v_) : nullptr,
-                  q_for_dk ? dout_dtype : p->v_dtype, q_for_dk ? gst : vst);
-      if (pl.k.ks != pl.q.ks)
-        prep_points_ks(c, k_, ks, N, pl.Np, pl.k.ks, pl.slots + 2, v_, p->v_dtype, vst);
-    } else {
-      prep_points(c, q_, qs, M, pl.Mp, pl.q, pl.slots + 2, one_c && grads ? g_ : nullptr, dout_dtype, gst);
-      prep_points(c, k_, ks, N, pl.Np, pl.k, pl.slots + 3, one_c ? v_ : nullptr, p->v_dtype, vst);
-    }
-    if (w.fwd || w.dq || w.dk) prep_values(c, v_, p->v_dtype, vst, N, pl.Np, pl.v, pl.slots + 0);
+    Prep prep(c);
+    // values and upstream gradients as the key scalars of the passes keyed by
+    // k and by q see them (single channel: magnitudes and signs)
+    const KeyScalars kv{pl.scal_kv, one_c ? v_ : nullptr, vst, (int)p->v_dtype, 0};
+    const KeyScalars qg{pl.scal_qg, one_c ? g_ : nullptr, gst, (int)dout_dtype, 1};
+    if (w.fwd || w.dq || w.dk) prep.maximum(0, v_, p->v_dtype, vst, N * C);
     // dout: its maximum scales the RT / KS copies (several channels, dv) and
     // enters the key scalars of passes keyed by q (dk, dv); a single-channel
     // dq reads dout exactly in its epilogue and needs none of it
-    if (grads && (C > 1 || w.dk || w.dv)) prep_values(c, g_, dout_dtype, gst, M, pl.Mp, pl.g, pl.slots + 1);
-    if (pl.scal_kv) prep_scalars(c, pl.k, v_, p->v_dtype, vst, N, pl.Np, pl.slots + 0, pl.scal_kv);
-    if (pl.scal_qg) prep_scalars(c, pl.q, g_, dout_dtype, gst, M, pl.Mp, pl.slots + 1, pl.scal_qg);
+    const bool need_g = grads && (C > 1 || w.dk || w.dv);
+    if (need_g) prep.maximum(1, g_, dout_dtype, gst, M * C);
+    prep.points(q_, qs, M, pl.Mp, pl.q, qg, alias ? kv : KeyScalars{});
+    if (!alias) prep.points(k_, ks, N, pl.Np, pl.k, kv, KeyScalars{});
+    // KS copies: q.ks serves dk (keys q, signs of dout) unless the points are
+    // one array and only dq wants a copy
+    if (pl.q.ks) prep.points_ks(q_, qs, M, pl.Mp, pl.q.ks, 2, alias && !w.dk ? kv : qg);
+    if (pl.k.ks && pl.k.ks != pl.q.ks) prep.points_ks(k_, ks, N, pl.Np, pl.k.ks, alias ? 2 : 3, kv);
+    if (w.fwd || w.dq || w.dk) prep.values(v_, p->v_dtype, vst, N, pl.Np, (int)C, pl.v, 0);
+    if (need_g) prep.values(g_, dout_dtype, gst, M, pl.Mp, (int)C, pl.g, 1);
+    prep.launch(row_flag_words(pl), kMaxParts);
     const uint32_t* kslot = alias ? pl.slots + 2 : pl.slots + 3;
     // full-sample row-bound flags for the forward-kernel passes (fwd, dv)
-    if (w.fwd && !w.fused()) row_check(c, pl.q, M, pl.Mp, pl.k);
-    if (w.dv && !w.fused_kv() && !(alias && w.fwd && !w.fused())) row_check(c, pl.k, N, pl.Np, pl.q);
+    const bool check_q = w.fwd && !w.fused(), check_k = w.dv && !w.fused_kv() && !(alias && check_q);
+    const CheckRows rq{&pl.q, M, pl.Mp, &pl.k}, rk{&pl.k, N, pl.Np, &pl.q};
+    if (check_q || check_k) row_check(c, check_q ? rq : rk, check_q && check_k ? rk : CheckRows());
     if (w.fwd && !w.fused()) pass_fwd(c, pl.q, M, pl.k, N, pl.scal_kv, pl.v.ks, pl.slots + 0, out_, os);
     if (w.dq)
       pass_dq(c, pl.q, M, pl.k, N, pl.scal_kv, kslot, pl.v.rt, pl.slots + 0, pl.g.rt, pl.slots + 1, g_,
@@ -1464,17 +1476,14 @@ gs_status gauss_sum_svgd(const gs_problem* p, const void* x, const void* score, 
     Plan& pl = sp.pl;
     const float tau2 = (float)(tau * 1.4426950408889634);
     Ctx c{stream, &sp.p1, &pl, tau, tau2, 1u, (int64_t)pl.total};
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, pl.slots, 16, 0u, Bz{});
-    // points: RT copy, half norms, sample, KS copy (plain: unit weights)
-    prep_points(c, x, 0, n, pl.Mp, pl.q, pl.slots + 2);
-    // scores: |max| and the KS copy (the values of the forward sum)
-    hipLaunchKernelGGL(k_absmax, dim3(grid_reduce(n * D)), dim3(256), 0, stream, score, n * D,
-                       (int)p->v_dtype, pl.slots + 0, Bz{});
-    hipLaunchKernelGGL(k_values_ks, dim3(grid1(pl.Np / 8 * sp.dm.Rv())), dim3(256), 0, stream, score,
-                       (int)p->v_dtype, n, (int)D, pl.Np, sp.dm.Rv(), (const uint32_t*)pl.slots + 0, 0,
-                       sp.score_ks, Bz{});
-    // key scalars: half norms only (unit weights)
-    prep_scalars(c, pl.q, nullptr, GS_F32, 0, n, pl.Np, pl.slots + 0, pl.scal_kv);
+    // points: RT copy, half norms, sample, KS copy, key scalars (plain: unit
+    // weights); scores: the KS copy (the values of the forward sum)
+    Prep prep(c);
+    prep.maximum(0, score, p->v_dtype, 0, n * D);
+    prep.points(x, 0, n, pl.Mp, pl.q, KeyScalars{pl.scal_kv, nullptr, 0, 0, 0}, KeyScalars{});
+    prep.points_ks(x, 0, n, pl.Mp, pl.q.ks, 2, KeyScalars{});
+    prep.values_ks(score, p->v_dtype, 0, n, pl.Np, (int)D, sp.dm.Rv(), sp.score_ks, 0, false);
+    prep.launch(row_flag_words(pl), kMaxParts);
     const PassShape& ps = sp.ps;
     const bool split = ps.splits > 1;
     prof_before(kKindGrad, stream);
@@ -1525,22 +1534,21 @@ gs_status gauss_sum_mmd_flow(const gs_problem* p, const void* x, const void* v, 
     }
     char* base = static_cast<char*>(workspace);
     const int64_t a = round_up(std::max<int64_t>(n, 1) * 4, 256);
-    float* ones = reinterpret_cast<float*>(base);
-    float* sbuf = reinterpret_cast<float*>(base + a);
-    double* parts = reinterpret_cast<double*>(base + 2 * a);
+    float* sbuf = reinterpret_cast<float*>(base);
+    double* parts = reinterpret_cast<double*>(base + a);
     const size_t extra = flow_extra(n);
     float* s_out = s ? s : (mmd2 ? sbuf : nullptr);
     if (n > 0) {
-      if (grad) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(n)), dim3(256), 0, stream, ones, n, 1.0f);
-      st = run(p, nullptr, x, x, v, tau, grad ? ones : nullptr, GS_F32, s_out, grad, nullptr, nullptr,
-               base + extra, workspace_bytes - extra, stream);
+      st = run(p, nullptr, x, x, v, tau, nullptr, GS_F32, s_out, grad, nullptr, nullptr, base + extra,
+               workspace_bytes - extra, stream, true);
       if (st != GS_SUCCESS) return st;
     }
     if (mmd2) {
-      hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, stream, v, (int)p->v_dtype,
-                         (const float*)s_out, n, parts);
-      hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(64), 0, stream, (const double*)parts, kDotBlocks,
-                         mmd2);
+      const int blocks = n <= kDotOneBlock ? 1 : (int)std::min<int64_t>(kDotBlocks, ceil_div(n, kDotThreads));
+      hipLaunchKernelGGL(k_dot, dim3(blocks), dim3(kDotThreads), 0, stream, v, (int)p->v_dtype, (const float*)s_out,
+                         n, blocks == 1 ? mmd2 : parts);
+      if (blocks > 1)
+        hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(256), 0, stream, (const double*)parts, blocks, mmd2);
     }
     return launch_status();
   } catch (...) {

@@ -24,148 +24,19 @@
 #pragma once
 
 #include "gs_kernels.h"
+#include "gs_prep.h"
 
 namespace gs {
 
-// Scale exponent of the split copies: max |x| 2^e in [2^14, 2^15).
-constexpr int kSplitHeadroom = 14;
 // Key steps per block of the blocked, compensated row sum.
 constexpr int kAccBlock = 16;
 
 // Queries per wave (16-row tiles) of the fp32-tier forward kernel.
 constexpr int f32_qt(int DP) { return DP >= 8 ? 1 : 8 / DP; }
 
-// fp32 points -> scaled hi / lo fp16 copies (RT layout) and fp32 half norms
-// -||x||^2/2 (exact fp32 inputs, squares summed in fp64).  Thread (r, c) moves
-// columns 8c .. 8c+7 of row r, as k_points_rt_norm (whole waves per row
-// group, so the shuffles are safe).  slot: max |x| bits (k_absmax).
-__global__ void k_points_split(const float* __restrict__ x, int64_t n, int D, int64_t n_pad, int W,
-                               const uint32_t* __restrict__ slot, uint16_t* __restrict__ hi,
-                               uint16_t* __restrict__ lo, float* __restrict__ nh, Bz bz) {
-  x = zoff(x, bz.in);
-  slot = zoff(slot, bz.ws);
-  hi = zoff(hi, bz.ws);
-  lo = zoff(lo, bz.ws);
-  nh = zoff(nh, bz.ws);
-  const int e = scale_exponent(*slot) + kSplitHeadroom;
-  const int cpr = W >> 3;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_pad * cpr; t += stride) {
-    const int64_t r = t / cpr;
-    const int c = (int)(t - r * cpr);
-    uint16_t h[8], l[8];
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int w = 8 * c + k;
-      const float xv = (r < n && w < D) ? x[r * D + w] : 0.0f;
-      acc += (double)xv * (double)xv;
-      const float xs = ldexpf(xv, e);
-      const _Float16 hh = (_Float16)xs;
-      h[k] = __builtin_bit_cast(uint16_t, hh);
-      l[k] = __builtin_bit_cast(uint16_t, (_Float16)(xs - (float)hh));
-    }
-    for (int off = cpr >> 1; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-    uint4 ph, pl;
-    ph.x = h[0] | ((uint32_t)h[1] << 16);
-    ph.y = h[2] | ((uint32_t)h[3] << 16);
-    ph.z = h[4] | ((uint32_t)h[5] << 16);
-    ph.w = h[6] | ((uint32_t)h[7] << 16);
-    pl.x = l[0] | ((uint32_t)l[1] << 16);
-    pl.y = l[2] | ((uint32_t)l[3] << 16);
-    pl.z = l[4] | ((uint32_t)l[5] << 16);
-    pl.w = l[6] | ((uint32_t)l[7] << 16);
-    *reinterpret_cast<uint4*>(hi + rt_index(r, 8 * c, W)) = ph;
-    *reinterpret_cast<uint4*>(lo + rt_index(r, 8 * c, W)) = pl;
-    if (c == 0) nh[r] = r < n ? (float)(-0.5 * acc) : kPadBias;
-  }
-}
-
-// Per-step scalars of the fp32 tier, 64 floats per 32-key step (v = NULL for
-// several value channels: the bias is the scaled half norm alone, signs +1):
-//   [0, 32)  2^(eq + ek) (b_n + log2 |v_n 2^ev| / tau'), the key bias in the
-//            scaled units of the split scores (-inf for padding keys and for
-//            v_n = 0: an exact zero term);
-//   [32, 64) sign(v_n) as +-1.0f, key 32 s + i at position 32 + i (the row
-//            order of the two 16-key score tiles).
-// slot_v / slot_q / slot_k: max |v|, max |q|, max |k| bits.  The bias is
-// formed in fp64 and rounded once (the fp32 log2 and its division would add
-// about one ulp of a systematic error to every term).
-__global__ void k_step_scalars32(const float* __restrict__ nh, const void* __restrict__ v, int dtype,
-                                 int64_t n, int64_t n_pad, const uint32_t* __restrict__ slot_v,
-                                 const uint32_t* __restrict__ slot_q, const uint32_t* __restrict__ slot_k,
-                                 float tau2, float* __restrict__ out, Bz bz) {
-  nh = zoff(nh, bz.ws);
-  v = zoff(v, bz.in);
-  slot_v = zoff(slot_v, bz.ws);
-  slot_q = zoff(slot_q, bz.ws);
-  slot_k = zoff(slot_k, bz.ws);
-  out = zoff(out, bz.ws);
-  const int ev = scale_exponent(*slot_v) - 1;
-  const int es = scale_exponent(*slot_q) + scale_exponent(*slot_k) + 2 * kSplitHeadroom;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_pad * 2; t += stride) {
-    const int64_t r = (t >> 6) * 32 + (t & 31);
-    float val;
-    if ((t & 63) < 32) {
-      val = -__builtin_inff();
-      if (r < n) {
-        const double lv = v ? log2(fabs((double)load_any(v, r, dtype))) + ev : 0.0;
-        val = (float)ldexp((double)nh[r] + lv / (double)tau2, es);
-      }
-    } else {
-      val = (v && r < n && load_any(v, r, dtype) < 0.0f) ? -1.0f : 1.0f;
-    }
-    out[t] = val;
-  }
-}
-
-// Values (several channels) for the fp32 tier: v 2^ev (max |v| 2^ev in [1, 2))
-// split into fp16 hi + lo, both in KS layout (R = C padded to 16), written as
-// k_values_ks does (eight key slots of one row per thread, 16-byte stores).
-__global__ void k_values_ks_split(const void* __restrict__ v, int dtype, int64_t n, int C, int64_t n_pad,
-                                  int R, const uint32_t* __restrict__ slot, uint16_t* __restrict__ vh,
-                                  uint16_t* __restrict__ vl, Bz bz) {
-  v = zoff(v, bz.in);
-  slot = zoff(slot, bz.ws);
-  vh = zoff(vh, bz.ws);
-  vl = zoff(vl, bz.ws);
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int ev = scale_exponent(*slot);
-  const int64_t total = (n_pad >> 5) * R * 4;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += stride) {
-    const int a = (int)(t & 3);
-    const int64_t rest = t >> 2;
-    const int64_t blk = rest / R;
-    const int w = (int)(rest - blk * R);
-    uint16_t h[8], l[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int z = 8 * a + e;
-      const int64_t r = blk * 32 + 16 * ((z & 7) >> 2) + 4 * (z >> 3) + (z & 3);
-      const float x = (r < n && w < C) ? ldexpf(load_any(v, r * C + w, dtype), ev) : 0.0f;
-      const _Float16 hh = (_Float16)x;
-      h[e] = __builtin_bit_cast(uint16_t, hh);
-      l[e] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)hh));
-    }
-    uint4 ph, pl;
-    ph.x = h[0] | ((uint32_t)h[1] << 16);
-    ph.y = h[2] | ((uint32_t)h[3] << 16);
-    ph.z = h[4] | ((uint32_t)h[5] << 16);
-    ph.w = h[6] | ((uint32_t)h[7] << 16);
-    pl.x = l[0] | ((uint32_t)l[1] << 16);
-    pl.y = l[2] | ((uint32_t)l[3] << 16);
-    pl.z = l[4] | ((uint32_t)l[5] << 16);
-    pl.w = l[6] | ((uint32_t)l[7] << 16);
-    const int64_t o = (blk * R + w) * 32 + 8 * a;
-    *reinterpret_cast<uint4*>(vh + o) = ph;
-    *reinterpret_cast<uint4*>(vl + o) = pl;
-  }
-}
-
 // s_m = sum_n Phi(q_m, k_n) v_n for fp32 points, C = 1 (see the top of this
 // file).  qh / ql, kh / kl: split copies (RT layout); nhq: query half norms;
-// scal: k_step_scalars32; slots: [0] max |v|, [2] max |q|, [3] max |k| (the
+// scal: key_scalars32; slots: [0] max |v|, [2] max |q|, [3] max |k| (the
 // key slot is [2] when q and k are the same array: kslot selects it).
 // Key steps are split over grid.y as in k_fwd (partials at part_stride);
 // problems of a batch on grid.z (strides of bz).

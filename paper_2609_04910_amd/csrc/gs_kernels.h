@@ -279,37 +279,40 @@ __device__ __forceinline__ bool needs_shift(const uint4* __restrict__ sample_rt,
 // small sample; the full-sample maximum is never below the coarse one, so rows
 // passing the coarse check pass the full one).  The forward kernel reads these
 // flags.
-// Key row of sample position pos (coarse positions first, as k_sample
-// stores them): rows floor(j N / kSampleRows).
-__device__ __forceinline__ int64_t sample_row(int pos, int64_t n) {
-  constexpr int kStride = kSampleRows / kSampleCoarse;
-  int j;
-  if (pos < kSampleCoarse) {
-    j = kStride * pos;
-  } else {
-    const int q = pos - kSampleCoarse;
-    j = (q / (kStride - 1)) * kStride + q % (kStride - 1) + 1;
-  }
-  return ((int64_t)j * n) / kSampleRows;
+//
+// One launch checks up to two directions: queries against keys, and (for the
+// passes keyed by the queries) keys against queries; workgroups below blocks0
+// take the first.
+struct CheckSide {
+  const uint4* qs;      // RT copy of the rows
+  const float* nhq;     // their half norms
+  const uint4* samp;    // sampled keys, RT layout
+  const float* samp_nh; // their half norms; the flags follow them (row_flags)
+  int64_t M;            // rows
+};
+
+// The flags of k_row_check for the rows queried against a sample are stored
+// right after that sample's half norms.
+__device__ __forceinline__ const uint32_t* row_flags(const float* sample_nh) {
+  return reinterpret_cast<const uint32_t*>(sample_nh + kSampleRows);
 }
 
-// GATHER: the sample is not copied; sample_rt / sample_nh are then the key
-// set's own RT copy and half norms (nk > 0 keys), and the sampled rows are
-// read from there (the same values k_sample would copy).
-template <typename T, int DP, bool GATHER>
-__global__ __launch_bounds__(kBlockThreads) void k_row_check(
-    const uint4* __restrict__ qs, const float* __restrict__ nhq, const uint4* __restrict__ sample_rt,
-    const float* __restrict__ sample_nh, float tau2, int64_t M, uint32_t* __restrict__ shift, Bz bz,
-    int64_t nk) {
+template <typename T, int DP>
+__global__ __launch_bounds__(kBlockThreads) void k_row_check(CheckSide a, CheckSide b, unsigned blocks0, float tau2,
+                                                             Bz bz) {
   constexpr int QT = 4;
-  qs = zoff(qs, bz.ws);
-  nhq = zoff(nhq, bz.ws);
-  sample_rt = zoff(sample_rt, bz.ws);
-  sample_nh = zoff(sample_nh, bz.ws);
-  shift = zoff(shift, bz.ws);
+  const bool first = blockIdx.x < blocks0;
+  const CheckSide sd = first ? a : b;
+  const uint4* __restrict__ qs = zoff(sd.qs, bz.ws);
+  const float* __restrict__ nhq = zoff(sd.nhq, bz.ws);
+  const uint4* __restrict__ sample_rt = zoff(sd.samp, bz.ws);
+  const float* __restrict__ sample_nh = zoff(sd.samp_nh, bz.ws);
+  uint32_t* __restrict__ shift = const_cast<uint32_t*>(row_flags(sample_nh));
+  const int64_t M = sd.M;
   const int lane = threadIdx.x & (kWave - 1);
   const int j = lane & 15, g = lane >> 4;
-  const int64_t q0 = ((int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * (16 * QT);
+  const int64_t q0 =
+      ((int64_t)(first ? blockIdx.x : blockIdx.x - blocks0) * kWavesPerBlock + threadIdx.x / kWave) * (16 * QT);
   uint4 qreg[QT][DP];
   float bq[QT], smax[QT];
 #pragma unroll
@@ -321,17 +324,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_row_check(
   auto scan = [&](int t0, int t1) {
     for (int t = t0; t < t1; ++t) {
       uint4 kr[DP];
-      floatx4 cin;
-      if constexpr (GATHER) {
-        const int64_t r = sample_row(16 * t + j, nk);
-#pragma unroll
-        for (int dc = 0; dc < DP; ++dc) kr[dc] = sample_rt[(((r >> 4) * DP + dc) * 16 + (r & 15)) * 4 + g];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) cin[u] = sample_nh[sample_row(16 * t + 4 * g + u, nk)];
-      } else {
-        load_k_tile<DP>(sample_rt, t, j, g, kr);
-        cin = *reinterpret_cast<const floatx4*>(sample_nh + 16 * t + 4 * g);
-      }
+      load_k_tile<DP>(sample_rt, t, j, g, kr);
+      const floatx4 cin = *reinterpret_cast<const floatx4*>(sample_nh + 16 * t + 4 * g);
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) smax[qt] = max_into(smax[qt], score_tile<T, DP>(kr, qreg[qt], cin));
     }
@@ -356,12 +350,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_row_check(
   if (g == 0)
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) shift[q0 + 16 * qt + j] = level[qt];
-}
-
-// The flags of k_row_check for the rows queried against a sample are stored
-// right after that sample's half norms.
-__device__ __forceinline__ const uint32_t* row_flags(const float* sample_nh) {
-  return reinterpret_cast<const uint32_t*>(sample_nh + kSampleRows);
 }
 
 // The largest k_row_check level (0, 1, 2) of the wave's 16 QT query rows.
@@ -1340,7 +1328,7 @@ __global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(2))
     } else {
       // single channel: w = g_m v_n with v_n 2^(ev-1) in the kernel values
       e = 1 - scale_exponent(*vslot);
-      f *= load_any(g1, m, g1_dtype);
+      if (g1) f *= load_any(g1, m, g1_dtype);  // NULL: unit upstream gradient
     }
     const float rm = rs[qt];
     const bool v4d = vec4_rows(out, D);
