@@ -16,6 +16,7 @@
 #include "gs_kernels.h"
 #include "gs_prep.h"
 #include "gs_f32.h"
+#include "gs_small.h"
 
 namespace gs {
 namespace {
@@ -341,6 +342,45 @@ const void* f32_pass_kernel(int64_t C, int DP) {
 }
 int f32_pass_qt(int64_t C, int DP) { return C == 1 ? f32_qt(DP) : f32c_qt(DP, f32c_ct(C)); }
 
+// Small problems (k_small): instances for D <= 128 and the values' chunks.
+using SmFn = void (*)(dim3, hipStream_t, const SmallSide&, const SmallSide&, unsigned, float, float, int, int);
+
+template <typename T, int DP, int CV, int KIND>
+void launch_small(dim3 grid, hipStream_t st, const SmallSide& a, const SmallSide& b, unsigned blocks0, float tau2,
+                  float tau, int D, int C) {
+  hipLaunchKernelGGL((k_small<T, DP, CV, KIND>), grid, dim3(kWave * small_waves(DP, CV, KIND)), 0, st, a, b, blocks0, tau2, tau, D, C);
+}
+
+template <typename T, int DP, int KIND>
+SmFn small_by_cv(int CV) {
+  switch (CV) {
+    case 0: if constexpr (KIND != kSmallSvgd) return &launch_small<T, DP, 0, KIND>; break;
+    case 1: if constexpr (KIND != kSmallSvgd || DP == 1) return &launch_small<T, DP, 1, KIND>; break;
+    // (bf16 keys at D > 64 with two value chunks would spill in the key loop)
+    case 2:
+      if constexpr ((KIND != kSmallSvgd || DP == 2) && !(DP == 4 && std::is_same<T, BF16>::value))
+        return &launch_small<T, DP, 2, KIND>;
+      break;
+  }
+  return nullptr;
+}
+
+template <typename T, int KIND>
+SmFn small_by_dp(int DP, int CV) {
+  switch (DP) {
+    case 1: return small_by_cv<T, 1, KIND>(CV);
+    case 2: return small_by_cv<T, 2, KIND>(CV);
+    case 4: if constexpr (KIND != kSmallSvgd) return small_by_cv<T, 4, KIND>(CV); break;
+  }
+  return nullptr;
+}
+
+template <typename T>
+SmFn small_fn_t(int DP, int CV, int kind) {
+  return kind == kSmallFwd ? small_by_dp<T, kSmallFwd>(DP, CV)
+                           : kind == kSmallGrad ? small_by_dp<T, kSmallGrad>(DP, CV) : small_by_dp<T, kSmallSvgd>(DP, CV);
+}
+
 // ------------------------------------------------------------ workspace plan
 
 struct Carver {
@@ -586,6 +626,50 @@ void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& p
   pl.part = part ? cv.take<float>(part) : nullptr;
   pl.part_s = part_s ? cv.take<float>(part_s) : nullptr;
   pl.total = cv.off;
+}
+
+// Whether one direction of a call (rows against keys, G problems) counts as
+// small: k_small then computes it in one launch.  Limits in tiles of 16 rows
+// x 32 keys, by kind, 32-wide chunks of D (1, 2, 4) and of the values (single
+// channel, 1, 2).  They lie where the two paths cross for M = N (us per call,
+// prepared path / k_small; 2^13 tiles are 2048^2, 2^15 are 4096^2):
+//   sum, D = 16, C = 1       2048: 24.3 / 15.1   4096: 24.2 / 18.0
+//   sum, D = 50, C = 1       2048: 24.0 / 16.0   4096: 23.5 / 24.2
+//   sum, D = 100, C = 1      1024: 23.3 / 17.3   2048: 23.9 / 24.3
+//   sum, D = 50, C = 10      2048: 27.1 / 20.3   3072: 26.6 / 26.9
+//   sum, D = 16, C = 50      3072: 38.1 / 32.0   4096: 45.0 / 40.0
+//   all, D = 10, C = 1       2048: 34.8 / 22.0   4096: 41.9 / 39.4
+//   all, D = 50, C = 1       2048: 49.8 / 22.1   4096: 78.8 / 59.1
+//   all, D = 100, C = 1      2048: 73.3 / 31.6   4096: 88.9 / 95.7
+//   all, D = 50, C = 10      2048: 45.7 / 24.2   4096: 74.3 / 73.1
+//   all, D = 100, C = 10     2048: 57.3 / 37.4   3072: 85.2 / 92.9
+//   all, D = 50, C = 50      2048: 80.3 / 33.0   4096: 135 / 103
+//   SVGD, D = 10             3072: 24.2 / 22.7   4096: 24.7 / 28.4
+//   SVGD, D = 45             1024: 25.4 / 21.5   2048: 28.9 / 32.4
+// Few key steps cost a workgroup at least as much as 32 of them (its queries'
+// loads, the reduction), and beyond 16 steps per wave the chain of steps is
+// longer than the prepared path's launches.
+bool small_side(int64_t rows, int64_t keys, int64_t G, int kind, int DP, int CV) {
+  constexpr int limit[3][3][3] = {
+      {{32768, 24576, 32768}, {18432, 14336, 8192}, {6144, 4096, 4096}},     // sum
+      {{24576, 16384, 32768}, {32768, 18432, 32768}, {16384, 10240, 18432}},  // gradient
+      {{0, 18432, 0}, {0, 0, 5120}, {0, 0, 0}}};                              // SVGD
+  const int dp = DP == 1 ? 0 : DP == 2 ? 1 : 2;
+  if (DP > 4 || CV > 2) return false;
+  const int64_t steps = ceil_div(keys, kStep);
+  return steps <= 16 * small_waves(DP, CV, kind) &&
+         ceil_div(rows, 16) * std::max<int64_t>(steps, 32) * G <= limit[kind][dp][CV];
+}
+
+inline int small_cv(const gs_problem& p, const Dims& dm, int kind) {
+  return p.C == 1 && kind != kSmallSvgd ? 0 : dm.CW;
+}
+
+// The k_small instance for a call of this shape, or NULL.
+SmFn small_fn(const gs_problem& p, const Dims& dm, int kind) {
+  if (p.qk_dtype == GS_F32) return nullptr;
+  const int cv = small_cv(p, dm, kind);
+  return p.qk_dtype == GS_F16 ? small_fn_t<F16>(dm.DP, cv, kind) : small_fn_t<BF16>(dm.DP, cv, kind);
 }
 
 // ------------------------------------------------------------ timing hook
@@ -1163,8 +1247,8 @@ int64_t group_size(const gs_problem& p, const Want& w, bool alias, int64_t cnt, 
 // workspace) before anything is enqueued, then runs the problems in launch
 // groups: prep kernels and passes for the requested outputs (out: forward
 // sum, dq / dk / dv: gradients; NULL = not requested), each launch covering a
-// whole group on grid.z.  unit_dout: an upstream gradient of ones (single
-// channel, dq only; dout is then NULL).
+// whole group on grid.z.  unit_dout: an MMD flow, whose upstream gradient is
+// ones (single channel, no dk or dv; dout is then NULL).
 gs_status run(const gs_problem* p, const gs_batch* b, const void* q, const void* k, const void* v,
               float tau, const void* dout, int dout_dtype, float* out, float* dq, float* dk,
               float* dv, void* workspace, size_t workspace_bytes, hipStream_t stream,
@@ -1268,6 +1352,38 @@ gs_status run(const gs_problem* p, const gs_batch* b, const void* q, const void*
   };
   const bool one_c = C == 1;
   const float tau2 = (float)(tau * 1.4426950408889634);
+  // small problems: a launch for each kind of direction, no preparation
+  const bool want_a = w.fwd || w.dq, want_b = w.dk || w.dv;
+  // (a flow's sum is the gradient kernel's whether or not the field is wanted)
+  const int kind_a = w.dq || unit_dout ? kSmallGrad : kSmallFwd, kind_b = w.dk ? kSmallGrad : kSmallFwd;
+  const SmFn fa = want_a ? small_fn(*p, pl.dm, kind_a) : nullptr;
+  const SmFn fb = want_b ? small_fn(*p, pl.dm, kind_b) : nullptr;
+  if ((!want_a || (fa && small_side(M, N, G, kind_a, pl.dm.DP, small_cv(*p, pl.dm, kind_a)))) &&
+      (!want_b || (fb && small_side(N, M, G, kind_b, pl.dm.DP, small_cv(*p, pl.dm, kind_b))))) {
+    for (int64_t g0 = 0; g0 < cnt; g0 += G) {
+      const unsigned n = (unsigned)std::min(G, cnt - g0);
+      auto u16 = [](const char* x) { return reinterpret_cast<const uint16_t*>(x); };
+      const SmallSide a{u16(at(q, g0, qs)), u16(at(k, g0, ks)), at(v, g0, vst), grads ? at(dout, g0, gst) : nullptr,
+                        at_o(out, g0, os), at_o(dq, g0, dqs), M, N, qs, ks, vst, gst, os, dqs,
+                        (int)p->v_dtype, (int)dout_dtype};
+      const SmallSide b{u16(at(k, g0, ks)), u16(at(q, g0, qs)), grads ? at(dout, g0, gst) : nullptr, at(v, g0, vst),
+                        at_o(dv, g0, dvs), at_o(dk, g0, dks), N, M, ks, qs, gst, vst, dvs, dks,
+                        (int)dout_dtype, (int)p->v_dtype};
+      const unsigned na = (unsigned)ceil_div(M, 16), nb = (unsigned)ceil_div(N, 16);
+      auto launch = [&](SmFn f, const SmallSide& x, const SmallSide& y, unsigned n0, unsigned total, int kind) {
+        prof_before(kind, stream);
+        f(dim3(total, 1, n), stream, x, y, n0, tau2, tau, (int)D, (int)C);
+        prof_after(kind, stream);
+      };
+      if (want_a && want_b && fa == fb) {
+        launch(fa, a, b, na, na + nb, kind_a == kSmallGrad ? kKindGrad : kKindFwd);
+      } else {
+        if (want_a) launch(fa, a, a, na, na, kind_a == kSmallGrad ? kKindGrad : kKindFwd);
+        if (want_b) launch(fb, b, b, nb, nb, kind_b == kSmallGrad ? kKindGrad : kKindFwd);
+      }
+    }
+    return launch_status();
+  }
   for (int64_t g0 = 0; g0 < cnt; g0 += G) {
     Ctx c{stream, p, &pl, tau, tau2, (unsigned)std::min(G, cnt - g0), (int64_t)pl.total};
     const void* q_ = at(q, g0, qs);
@@ -1475,6 +1591,15 @@ gs_status gauss_sum_svgd(const gs_problem* p, const void* x, const void* score, 
     svgd_plan(*p, workspace, sp);
     Plan& pl = sp.pl;
     const float tau2 = (float)(tau * 1.4426950408889634);
+    if (const SmFn f = small_side(n, n, 1, kSmallSvgd, sp.dm.DP, sp.dm.CW) ? small_fn(*p, sp.dm, kSmallSvgd) : nullptr) {
+      const SmallSide a{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(x), score, nullptr, nullptr, phi,
+                        n, n, 0, 0, 0, 0, 0, 0, (int)p->v_dtype, 0};
+      const unsigned blocks = (unsigned)ceil_div(n, 16);
+      prof_before(kKindGrad, stream);
+      f(dim3(blocks), stream, a, a, blocks, tau2, tau, (int)D, (int)D);
+      prof_after(kKindGrad, stream);
+      return launch_status();
+    }
     Ctx c{stream, &sp.p1, &pl, tau, tau2, 1u, (int64_t)pl.total};
     // points: RT copy, half norms, sample, KS copy, key scalars (plain: unit
     // weights); scores: the KS copy (the values of the forward sum)
