@@ -241,9 +241,8 @@ __device__ __forceinline__ void load_k_tile_lds(const uint4* base, int tile, int
 // sample_rt / sample_nh: the sampled keys (RT layout, half norms, coarse
 // sample first).  Returns whether some query of the wave has its sampled row
 // maximum of the log2 kernel value below kShiftBelow over the coarse sample;
-// the gradient kernel then takes the exact row maxima (a clustered key set
-// only costs it time).  The forward kernel reads the per-row levels of
-// k_row_check instead.
+// sampled_or_exact_offsets then looks closer.  The forward kernel reads the
+// per-row levels of k_row_check instead.
 template <typename T, int DP, int QT>
 __device__ __forceinline__ bool needs_shift(const uint4* __restrict__ sample_rt,
                                             const float* __restrict__ sample_nh,
@@ -361,33 +360,56 @@ __device__ __forceinline__ int wave_shift_level(const uint32_t* __restrict__ shi
   return __any(f >= 2u) ? 2 : __any(f >= 1u) ? 1 : 0;
 }
 
-// Exact row maxima of S~ over the wave's key range, from the RT key copy in
-// global memory (identical MFMA inputs and order as the main loop).
-template <typename T, int DP, int QT>
-__device__ __forceinline__ void exact_offsets(const uint4* __restrict__ ks, const float* __restrict__ scal,
-                                           const uint4 (&qreg)[QT][DP], int s_begin, int s_end,
-                                           int j, int g, float tau2, float (&bq)[QT], float (&off)[QT]) {
-  float smax[QT];
+// Offsets of a wave that failed the coarse check.  First pass: the whole
+// sample (a clustered key set hides a row's own cluster from 64 keys: with 32
+// clusters 13 % of the rows, so nearly every 64-query wave); where every
+// row's sampled maximum reaches kShiftBelow the offsets stay 0, as in the
+// forward kernel.  Otherwise a second pass over the wave's own key range takes
+// the exact row maxima (identical MFMA inputs and order as the main loop).
+// M = N = 32768, D = 32, C = 4, 32 clusters, tau = 1, sum and gradients: 1049 ->
+// 655 us.  Not at D > 128 (SCAN = false: the second pass only): any more code
+// here pushes spills into the key loop of the instance with a fused sum
+// (M = 2^15, N = 2^18, C = 16: 14.7 -> 32 ms).
+template <typename T, int DP, int QT, bool SCAN>
+__device__ __forceinline__ void sampled_or_exact_offsets(const uint4* __restrict__ samp_rt,
+                                                      const float* __restrict__ samp_nh,
+                                                      const uint4* __restrict__ ks, const float* __restrict__ scal,
+                                                      const uint4 (&qreg)[QT][DP], int s_begin, int s_end,
+                                                      int64_t q0, int64_t M, int j, int g, float tau2,
+                                                      float (&bq)[QT], float (&off)[QT]) {
+  const uint4* keys = SCAN ? samp_rt : ks + (int64_t)s_begin * (2 * DP * 64);
+  const float* bias = SCAN ? samp_nh : scal + (int64_t)s_begin * kScalarFloats;
+  int stride = SCAN ? kStep : kScalarFloats, steps = SCAN ? kSampleRows / kStep : s_end - s_begin;
+  for (int pass = SCAN ? 0 : 1; pass < 2; ++pass) {
+    float smax[QT];
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) smax[qt] = -__builtin_inff();
-  for (int s = s_begin; s < s_end; ++s) {
+    for (int qt = 0; qt < QT; ++qt) smax[qt] = -__builtin_inff();
+    for (int s = 0; s < steps; ++s) {
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      uint4 kr[DP];
-      load_k_tile<DP>(ks, 2 * (int64_t)s + kt, j, g, kr);
-      const floatx4 cin =
-          *reinterpret_cast<const floatx4*>(scal + (int64_t)s * kScalarFloats + 16 * kt + 4 * g);
+      for (int kt = 0; kt < 2; ++kt) {
+        uint4 kr[DP];
+        load_k_tile<DP>(keys, 2 * (int64_t)s + kt, j, g, kr);
+        const floatx4 cin = *reinterpret_cast<const floatx4*>(bias + (int64_t)s * stride + 16 * kt + 4 * g);
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-        smax[qt] = max_into(smax[qt], score_tile<T, DP>(kr, qreg[qt], cin));
+        for (int qt = 0; qt < QT; ++qt)
+          smax[qt] = max_into(smax[qt], score_tile<T, DP>(kr, qreg[qt], cin));
+      }
     }
+    bool low = false;
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      const float L = fmaf(wave_max_over_g(smax[qt]), tau2, bq[qt]);
+      low |= (q0 + 16 * qt + j < M) && (L < kShiftBelow);
+      off[qt] = pass == 0 || !(L > -__builtin_inff()) ? 0.0f : L;  // (-inf: empty key range)
+    }
+    if (pass == 0 && !__any(low)) break;
+    keys = ks + (int64_t)s_begin * (2 * DP * 64);
+    bias = scal + (int64_t)s_begin * kScalarFloats;
+    stride = kScalarFloats;
+    steps = s_end - s_begin;
   }
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    off[qt] = fmaf(wave_max_over_g(smax[qt]), tau2, bq[qt]);
-    if (!(off[qt] > -__builtin_inff())) off[qt] = 0.0f;  // empty key range
-    bq[qt] -= off[qt];
-  }
+  for (int qt = 0; qt < QT; ++qt) bq[qt] -= off[qt];
 }
 
 // acc + sum over the 8 fp16 products a_i b_i (v_dot2_f32_f16, fp32 accumulation).
@@ -970,7 +992,7 @@ __global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(2))
     off[qt] = 0.0f;
   }
   if (needs_shift<T, DP, QT>(samp_rt, samp_nh, qreg, bq, tau2, q0, M, j, g))
-    exact_offsets<T, DP, QT>(ks, scal, qreg, s_begin, s_end, j, g, tau2, bq, off);
+    sampled_or_exact_offsets<T, DP, QT, DP <= 4>(samp_rt, samp_nh, ks, scal, qreg, s_begin, s_end, q0, M, j, g, tau2, bq, off);
   if constexpr (CW > 0) settle(greg);
 
   floatx4 dQ[QT][DT];
