@@ -62,9 +62,14 @@ inline Dims dims_of(int64_t D, int64_t C) {
   return d;
 }
 
-// Query tiles per wave.  Forward: 8 for D <= 64 with C <= 32 (the per-step
+// Query tiles per wave.  Forward: 8 for 32 < D <= 64 with C <= 32 (the per-step
 // barrier, loads and K-tile reads then cover twice the pairs: D = 64, C = 1
-// 0.76 -> 0.71 ms), else the largest of 4, 2, 1 whose kernel (as compiled
+// 0.76 -> 0.71 ms); 4 for D <= 32, where eight took 160 registers and three
+// waves per SIMD and four take 92 and five waves: the online mode's check,
+// a branch per tile, then has other waves to hide behind (M = N = 131072,
+// C = 4, 32 clusters, tau = 10: 2797 -> 2537 us; plain, B = 64 problems of
+// 16384, C = 1: 2124 / 2127 us), and smaller problems split into more, shorter
+// workgroups (M = N = 10000, C = 1: 51 -> 35 us); else the largest of 4, 2, 1 whose kernel (as compiled
 // for gfx950) keeps the register count at or below 256 per lane (two waves
 // per SIMD).  Gradient: for D > 64 two tiles even where that needs the
 // occupancy hint on k_dq or (D = 256, whose LDS ring allows one workgroup per
@@ -78,7 +83,7 @@ inline Dims dims_of(int64_t D, int64_t C) {
 // (C > 128: two tiles at every D, and D <= 64 with C = 65 - 128: four,
 // the operands read as they are used.)
 constexpr int fwd_qt(int DP, int CT) {
-  return CT >= 16 ? 2 : CT == 8 ? (DP <= 2 ? 4 : 2) : (DP == 8 && CT > 1) ? 2 : (DP <= 2 && CT <= 2) ? 8 : 4;
+  return CT >= 16 ? 2 : CT == 8 ? (DP <= 2 ? 4 : 2) : (DP == 8 && CT > 1) ? 2 : (DP == 2 && CT <= 2) ? 8 : 4;
 }
 // Every workgroup's rows lie inside the padded row range.
 static_assert(kRowPad % (kBlockThreads / 4 * 8) == 0 && kRowPad % 256 == 0, "row padding vs. query tiles");

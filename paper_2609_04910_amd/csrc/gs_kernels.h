@@ -578,7 +578,9 @@ __global__ __launch_bounds__(kWave * WPB) void k_fwd(
   // every chunk, waves 4-7 none (splitting the copies between the two groups
   // measured slower)
   constexpr bool WIDE = WPB == 2 * kWavesPerBlock;
-  constexpr int NS = WIDE ? wide_stages(STAGE, NCH + 1) : ring_stages(STAGE, NCH + 1);
+  // D <= 32 with one value tile: a step is short (four query tiles of it take
+  // about 540 cycles), so four stages (13 KiB; 1 - 2 % over three)
+  constexpr int NS = DP == 1 && CT == 1 ? 4 : WIDE ? wide_stages(STAGE, NCH + 1) : ring_stages(STAGE, NCH + 1);
   __shared__ __attribute__((aligned(1024))) char lds[NS * STAGE];
 
   const int lane = threadIdx.x & (kWave - 1);
