@@ -172,17 +172,25 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32(
 
 namespace gs {
 
-// Several value channels (fp32 points, C > 1).  Two passes over the wave's
-// keys through the LDS ring.  The first takes the exact row maximum of the
-// exponent, with the same split scores as the second, so the largest scaled
-// value of a row is exactly 2^kPScale.  The second evaluates
-// P' = 2^(x - off + kPScale) in fp32, splits it into fp16 hi + lo (hi = P'
-// rounded, lo = P' - hi rounded; the scale keeps lo out of the fp16
-// subnormals for every value within 2^-14 of the row maximum) and contracts
-// with the split values (v 2^ev = vh + vl): vh.Ph into a block accumulator
-// that is added to the running sum with Kahan's compensation every kAccBlock
-// steps, vl.Ph + vh.Pl (about 2^-11 of it) into a second accumulator.
-constexpr int kPScale = 11;
+// Several value channels (fp32 points, C > 1).  One pass over the wave's keys
+// through the LDS ring.  P = 2^(x - off) is evaluated in fp32, split into fp16
+// hi + lo 2^-kSplitLow (hi = P rounded, lo = (P - hi) 2^kSplitLow rounded) and
+// contracted with the values, split the same way (v 2^ev = vh + vl 2^-kSplitLow):
+// vh.Ph into a block accumulator that is added to the running sum with Kahan's
+// compensation every kAccBlock steps, vl.Ph + vh.Pl into a second accumulator
+// in units of 2^-kSplitLow.
+//
+// off is a running offset per row: the row's largest exponent, rounded down to
+// a whole number, at the last step in which some exponent of the row exceeded
+// the offset by more than kPRaise.  So P stays below 2^5; hi and lo together
+// resolve 2^-36 of the row maximum or better, as with an exact maximum; the
+// exponents that matter are small numbers, which fp32 rounds least; and whole
+// offsets make every rescaling of the accumulators exact.  (A first pass over
+// all keys for the exact maxima computed every split score, three MFMAs per
+// operand pair, a second time: B = 4, M = N = 16384, D = C = 32
+// 650 -> 473 us, D = 100, C = 5 657 -> 296 us, M = N = 16384; error against 64
+// bits 3.4e-7 -> 1.8e-7, from the smaller exponents.)
+constexpr float kPRaise = 4.0f;
 // Queries per wave (16-row tiles) of the several-channel kernel.
 constexpr int f32c_qt(int DP, int CT) { return (DP >= 4 || CT >= 4) ? 1 : 2; }
 // Channels per launch of the several-channel kernel (16 * CT at most).
@@ -237,8 +245,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
                              nsteps * (uint32_t)vstep);
   const auto rsc = make_rsrc(scal + (int64_t)s_begin * kScalarFloats, nsteps * kScalarFloats * 4);
   const uint32_t lds0 = lds_address(lds);
-  // first pass: keys and scalars only
-  auto issue_k = [&](int s, int stage) {
+  auto issue = [&](int s, int stage) {
     if (!mine) return;
     const uint32_t base = lds0 + stage * STAGE;
     const uint32_t ls = (uint32_t)(s - s_begin);
@@ -246,31 +253,24 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
     for (int c = 0; c < KCH; ++c) dma_x4(rkh, (ls * KCH + c) * 1024, base + c * 1024, dlane);
 #pragma unroll
     for (int c = 0; c < KCH; ++c) dma_x4(rkl, (ls * KCH + c) * 1024, base + (KCH + c) * 1024, dlane);
-    dma_x1(rsc, ls * kScalarFloats * 4, base + NCH * 1024, 4 * lane);
-  };
-  auto issue_all = [&](int s, int stage) {
-    issue_k(s, stage);
-    if (!mine) return;
-    const uint32_t base = lds0 + stage * STAGE;
-    const uint32_t ls = (uint32_t)(s - s_begin);
 #pragma unroll
     for (int c = 0; c < CT; ++c)
       dma_x4(rvh, ls * (uint32_t)vstep + c * 1024, base + (2 * KCH + c) * 1024, dlane);
 #pragma unroll
     for (int c = 0; c < CT; ++c)
       dma_x4(rvl, ls * (uint32_t)vstep + c * 1024, base + (2 * KCH + CT + c) * 1024, dlane);
+    dma_x1(rsc, ls * kScalarFloats * 4, base + NCH * 1024, 4 * lane);
   };
 
   const int es = scale_exponent(slots[2]) + scale_exponent(slots[kslot]) + 2 * kSplitHeadroom;
   const float tau2s = ldexpf(tau2, -es);
   uint4 qhr[QT][DP], qlr[QT][DP];
-  float bq[QT], smax[QT];
+  float bq[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     load_k_tile<DP>(qh, q0 / 16 + qt, j, g, qhr[qt]);
     load_k_tile<DP>(ql, q0 / 16 + qt, j, g, qlr[qt]);
     bq[qt] = tau2 * nhq[q0 + 16 * qt + j];
-    smax[qt] = -__builtin_inff();
   }
   settle(qhr);
   settle(qlr);
@@ -287,36 +287,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
     return acc;
   };
 
-  // pass 1: exact row maxima of the scaled score
-  auto compute_max = [&](int stage) {
-    const char* base = lds + stage * STAGE;
-    const uint4* khb = reinterpret_cast<const uint4*>(base);
-    const uint4* klb = reinterpret_cast<const uint4*>(base + KCH * 1024);
-    const float* sc = reinterpret_cast<const float*>(base + NCH * 1024);
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const floatx4 cin = *reinterpret_cast<const floatx4*>(sc + 16 * kt + 4 * g);
-      uint4 khr[DP], klr[DP];
-      load_k_tile_lds<DP>(khb, kt, j, g, khr);
-      load_k_tile_lds<DP>(klb, kt, j, g, klr);
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) smax[qt] = max_into(smax[qt], score(khr, klr, qt, cin));
-    }
-  };
-  key_stream<NS, 2 * KCH + 1>(s_begin, s_end, issue_k, compute_max);
-  // every wave is done with the ring before the second pass refills it
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  float off[QT];
+  // offsets, and the constant term of the exponent relative to them
+  float off[QT], be[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
-    off[qt] = fmaf(wave_max_over_g(smax[qt]), tau2s, bq[qt]);
-    if (!(off[qt] > -__builtin_inff())) off[qt] = 0.0f;  // empty key range
-    bq[qt] = bq[qt] - off[qt] + (float)kPScale;
+    off[qt] = -__builtin_inff();
+    be[qt] = __builtin_inff();
   }
-
-  // pass 2
   floatx4 O1[QT][CT], O2[QT][CT], T[QT][CT], Tc[QT][CT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt)
@@ -352,7 +329,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
       vhr[ct] = vhb[(16 * ct + j) * 4 + lds_col(j, g)];
       vlr[ct] = vlb[(16 * ct + j) * 4 + lds_col(j, g)];
     }
-    float p[QT][2][4];
+    floatx4 sc2[QT][2];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
       const floatx4 cin = *reinterpret_cast<const floatx4*>(sc + 16 * kt + 4 * g);
@@ -360,21 +337,60 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
       load_k_tile_lds<DP>(khb, kt, j, g, khr);
       load_k_tile_lds<DP>(klb, kt, j, g, klr);
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        const floatx4 acc = score(khr, klr, qt, cin);
+      for (int qt = 0; qt < QT; ++qt) sc2[qt][kt] = score(khr, klr, qt, cin);
+    }
+    float p[QT][2][4];
+    float ymax = -__builtin_inff();
+    auto exponents = [&](int qt) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[qt][kt][r] = __builtin_amdgcn_exp2f(fmaf(acc[r], tau2s, bq[qt]));
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[qt][kt][r] = fmaf(sc2[qt][kt][r], tau2s, be[qt]);
+    };
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      exponents(qt);
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+        ymax = max_into(ymax, floatx4{p[qt][kt][0], p[qt][kt][1], p[qt][kt][2], p[qt][kt][3]});
+    }
+    if (__any(ymax > kPRaise)) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        float raw = -__builtin_inff();
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) raw = max_into(raw, sc2[qt][kt]);
+        // (finite also where every exponent so far is -inf)
+        const float nw = fmaxf(fmaxf(off[qt], -3.0e38f), floorf(fmaf(wave_max_over_g(raw), tau2s, bq[qt])));
+        const float f = nw > off[qt] ? exp2f(off[qt] - nw) : 1.0f;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            O1[qt][ct][r] *= f;
+            O2[qt][ct][r] *= f;
+            T[qt][ct][r] *= f;
+            Tc[qt][ct][r] *= f;
+          }
+        off[qt] = nw;
+        be[qt] = bq[qt] - nw;
+        exponents(qt);
       }
     }
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[qt][kt][r] = __builtin_amdgcn_exp2f(p[qt][kt][r]);
       const uint4 bh = pack_tile_pair(p[qt]);
       const uint32_t hw[4] = {bh.x, bh.y, bh.z, bh.w};
       float lo[2][4];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const halfx2 h2 = __builtin_bit_cast(halfx2, hw[e >> 1]);
-        lo[e >> 2][e & 3] = p[qt][e >> 2][e & 3] - (float)h2[e & 1];
+        // (exact: both products are, and the difference)
+        lo[e >> 2][e & 3] = fmaf((float)h2[e & 1], -kSplitLowScale, p[qt][e >> 2][e & 3] * kSplitLowScale);
       }
       const uint4 bl = pack_tile_pair(lo);
 #pragma unroll
@@ -389,7 +405,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
       in_block = 0;
     }
   };
-  key_stream<NS, NCH + 1>(s_begin, s_end, issue_all, compute);
+  key_stream<NS, NCH + 1>(s_begin, s_end, issue, compute);
   close_block();
 
   const int ev = scale_exponent(slots[0]);
@@ -397,17 +413,16 @@ __global__ __launch_bounds__(kBlockThreads) void k_fwd32c(
   for (int qt = 0; qt < QT; ++qt) {
     const int64_t m = q0 + 16 * qt + j;
     if (m >= M) continue;
-    // 2^(off - kPScale - ev), the integer part through ldexp (no denormal factor)
-    const float fo = floorf(off[qt]);
-    const float f = exp2f(off[qt] - fo);
-    const int e = (int)fo - kPScale - ev;
+    // 2^(off - ev) through ldexp (no denormal factor; offsets beyond
+    // any result's range, and that of an empty key range, bounded)
+    const int e = (int)fmaxf(off[qt], -1.0e6f) - ev;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int c = 16 * ct + 4 * g + r;
-        const float x = (T[qt][ct][r] - Tc[qt][ct][r]) + O2[qt][ct][r];
-        if (c < cw) out[m * C + c] = ldexpf(x * f, e);
+        const float x = fmaf(O2[qt][ct][r], 1.0f / kSplitLowScale, T[qt][ct][r] - Tc[qt][ct][r]);
+        if (c < cw) out[m * C + c] = ldexpf(x, e);
       }
   }
 }

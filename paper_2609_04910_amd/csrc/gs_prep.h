@@ -352,7 +352,10 @@ __device__ __forceinline__ void key_scalars32(float* __restrict__ scal, float ha
 }
 
 // Values (several channels) for the fp32 tier: v 2^ev (max |v| 2^ev in [1, 2))
-// split into fp16 hi + lo, both in KS layout, written as values_ks_item does.
+// split into fp16 hi + lo 2^-kSplitLow (scaled so that lo stays out of the
+// subnormals), both in KS layout, written as values_ks_item does.
+constexpr int kSplitLow = 11;
+constexpr float kSplitLowScale = (float)(1 << kSplitLow);
 __device__ __forceinline__ void values_ks_split_item(const void* __restrict__ v, int dtype, int64_t n, int C,
                                                      int lgR, int ev, uint16_t* __restrict__ vh,
                                                      uint16_t* __restrict__ vl, int64_t t) {
@@ -367,7 +370,7 @@ __device__ __forceinline__ void values_ks_split_item(const void* __restrict__ v,
     const float x = (r < n && w < C) ? ldexpf(load_any(v, r * C + w, dtype), ev) : 0.0f;
     const _Float16 hh = (_Float16)x;
     h[e] = __builtin_bit_cast(uint16_t, hh);
-    l[e] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)hh));
+    l[e] = __builtin_bit_cast(uint16_t, (_Float16)((x - (float)hh) * kSplitLowScale));
   }
   *reinterpret_cast<uint4*>(vh + (rest * 32 + 8 * a)) = pack8(h);
   *reinterpret_cast<uint4*>(vl + (rest * 32 + 8 * a)) = pack8(l);
