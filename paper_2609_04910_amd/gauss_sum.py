@@ -197,7 +197,7 @@ def gauss_sum_fwd_bwd_workspace_size(M, N, D, C, qk_dtype=GS_F16, v_dtype=GS_F32
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check_inputs(q, k, v):
@@ -266,7 +266,14 @@ def _stream_of(stream):
 
 
 def _stream(stream):
-    return ctypes.c_void_p(_stream_of(stream).cuda_stream)
+    """The raw stream handle.  For the current stream the handle alone is
+    asked for where torch has a call for it (0.3 us; a Stream object takes 3)."""
+    if stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
+    return _stream_of(stream).cuda_stream
 
 
 def _keep_alive(stream, *tensors):
@@ -274,8 +281,10 @@ def _keep_alive(stream, *tensors):
     enqueued on another `stream`: mark them as in use on that stream, so the
     caching allocator does not hand their memory out again before those
     kernels finish."""
+    if stream is None:
+        return
     import torch
-    if stream is None or stream == torch.cuda.current_stream():
+    if stream == torch.cuda.current_stream():
         return
     for t in tensors:
         if t is not None:
