@@ -636,33 +636,41 @@ void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& p
 // Whether one direction of a call (rows against keys, G problems) counts as
 // small: k_small then computes it in one launch.  Limits in tiles of 16 rows
 // x 32 keys, by kind, 32-wide chunks of D (1, 2, 4) and of the values (single
-// channel, 1, 2).  They lie where the two paths cross for M = N (us per call,
-// prepared path / k_small; 2^13 tiles are 2048^2, 2^15 are 4096^2):
-//   sum, D = 16, C = 1       2048: 24.3 / 15.1   4096: 24.2 / 18.0
-//   sum, D = 50, C = 1       2048: 24.0 / 16.0   4096: 23.5 / 24.2
-//   sum, D = 100, C = 1      1024: 23.3 / 17.3   2048: 23.9 / 24.3
-//   sum, D = 50, C = 10      2048: 27.1 / 20.3   3072: 26.6 / 26.9
-//   sum, D = 16, C = 50      3072: 38.1 / 32.0   4096: 45.0 / 40.0
-//   all, D = 10, C = 1       2048: 34.8 / 22.0   4096: 41.9 / 39.4
-//   all, D = 50, C = 1       2048: 49.8 / 22.1   4096: 78.8 / 59.1
-//   all, D = 100, C = 1      2048: 73.3 / 31.6   4096: 88.9 / 95.7
-//   all, D = 50, C = 10      2048: 45.7 / 24.2   4096: 74.3 / 73.1
-//   all, D = 100, C = 10     2048: 57.3 / 37.4   3072: 85.2 / 92.9
-//   all, D = 50, C = 50      2048: 80.3 / 33.0   4096: 135 / 103
-//   SVGD, D = 10             3072: 24.2 / 22.7   4096: 24.7 / 28.4
-//   SVGD, D = 45             1024: 25.4 / 21.5   2048: 28.9 / 32.4
+// channel, 1, 2).  They lie below where the two paths cross for M = N (us per
+// call, prepared path / k_small; 2^13 tiles are 2048^2, 2^15 are 4096^2), and
+// no higher than the sizes that were compared:
+//   sum, D = 16, C = 1       4000: 22.0 / 13.4   5000: 22.6 / 28.3
+//   sum, D = 50, C = 1       3000: 23.4 / 15.1   4000: 24.0 / 18.1
+//   sum, D = 100, C = 1      1024: 23.3 / 13.0   2048: 23.3 / 19.1
+//   sum, D = 16, C = 10      3000: 24.2 / 18.3   4000: 24.3 / 22.3
+//   sum, D = 50, C = 10      2048: 24.6 / 16.9   3000: 26.3 / 21.7
+//   sum, D = 50, C = 50      3000: 34.3 / 28.7   4000: 43.1 / 37.2
+//   sum, D = 100, C = 10     1024: 24.1 / 15.7   2048: 26.0 / 23.4
+//   all, D = 10, C = 1       3000: 34.3 / 28.5   4000: 42.4 / 34.3
+//   all, D = 10, C = 10      2048: 36.1 / 19.8   3000: 41.6 / 40.4 (bf16 42.1 / 43.2)
+//   all, D = 10, C = 50      4000:  104 / 66.6   5000:  127 / 115
+//   all, D = 50, C = 1       3000: 58.8 / 39.1   4000: 76.3 / 48.5
+//   all, D = 50, C = 10      3000: 59.6 / 49.6   4000: 73.9 / 61.8
+//   all, D = 50, C = 50      3000:  104 / 63.6   4000:  132 / 79.3
+//   all, D = 100, C = 1      2048: 74.2 / 24.9   3000: 83.6 / 60.8 (bf16 86.7 / 68.8)
+//   all, D = 100, C = 10     2048: 58.3 / 29.0 (bf16 60.4 / 39.7)
+//   all, D = 100, C = 50     2048:  102 / 46.9   3072:  139 / 117
+//   SVGD, D = 10             2048: 21.2 / 16.0   3000: 21.6 / 20.2
+//   SVGD, D = 45             1024: 25.4 / 18.6   2048: 29.0 / 28.0
+// A sum over D <= 32 has sixteen waves and then one workgroup per CU: beyond
+// 4096 rows a second round begins.
 // Few key steps cost a workgroup at least as much as 32 of them (its queries'
-// loads, the reduction), and beyond 16 steps per wave the chain of steps is
+// loads, the reduction), and beyond 24 steps per wave the chain of steps is
 // longer than the prepared path's launches.
 bool small_side(int64_t rows, int64_t keys, int64_t G, int kind, int DP, int CV) {
   constexpr int limit[3][3][3] = {
-      {{32768, 24576, 32768}, {18432, 14336, 8192}, {6144, 4096, 4096}},     // sum
-      {{24576, 16384, 32768}, {32768, 18432, 32768}, {16384, 10240, 18432}},  // gradient
-      {{0, 18432, 0}, {0, 0, 5120}, {0, 0, 0}}};                              // SVGD
+      {{32768, 32768, 45000}, {32768, 30000, 32768}, {14336, 8192, 8192}},    // sum
+      {{32768, 16384, 49152}, {32768, 32768, 45000}, {24576, 16384, 16384}},  // gradient
+      {{0, 24576, 0}, {0, 0, 14336}, {0, 0, 0}}};                             // SVGD
   const int dp = DP == 1 ? 0 : DP == 2 ? 1 : 2;
   if (DP > 4 || CV > 2) return false;
   const int64_t steps = ceil_div(keys, kStep);
-  return steps <= 16 * small_waves(DP, CV, kind) &&
+  return steps <= 24 * small_waves(DP, CV, kind) &&
          ceil_div(rows, 16) * std::max<int64_t>(steps, 32) * G <= limit[kind][dp][CV];
 }
 

@@ -19,11 +19,15 @@
 // step is computed.  At the end the waves' partial results are added in wave
 // order through LDS, so results are reproducible bit for bit.
 //
-// Bound by instruction issue and latency, not by memory: a step of one wave
-// takes 0.3 - 0.9 us of its SIMD, several times the prepared kernels' (norms,
-// conversions and masks per step), which is why larger calls prepare.  Key
-// steps started at different places by different workgroups (so that they do
-// not wait for the same cold lines) measured the same and are not used.
+// Bound by instruction issue and latency, not by memory: per step the norms,
+// conversions and masks take several times the prepared kernels' instructions,
+// which is why larger calls prepare.  What that share cost and no longer does
+// (sum over 4096 x 4096, D = 16, C = 1, the kernel alone): branches on the
+// values' type per element and on a divergent wave index 27 -> 18 us; masks as
+// scalar pairs and element-by-element loads at the arrays' ends 18 -> 13 us.
+// Norms in fp32 would save 5 % and lose precision; key steps started at
+// different places by different workgroups (so that they do not wait for the
+// same cold lines) measured the same.
 //
 // Range: kernel values carry a running offset per row and wave (the row's
 // largest exponent, rounded down, when it last grew by more than kSmallRaise), so no row
@@ -81,58 +85,87 @@ __device__ __forceinline__ Raw8 load8_any(const void* __restrict__ x, int esize,
   const char* p = static_cast<const char*>(x) + idx * esize;
   return Raw8{load16(p), load16(p + 16)};
 }
-// Elements idx .. idx+7 near the end of an array of `count` elements: only
-// elements inside it are read (one by one, all loads in flight together), those from `valid`
-// on are zero.
-__device__ __forceinline__ uint4 load8_u16_part(const uint16_t* __restrict__ x, int64_t idx, int64_t count, int valid) {
-  uint32_t h[8], w[4];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = x[idx + e < count ? idx + e : count - 1];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = e < valid ? h[e] : 0u;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) w[e] = h[2 * e] | (h[2 * e + 1] << 16);
-  return uint4{w[0], w[1], w[2], w[3]};
-}
-__device__ __forceinline__ Raw8 load8_any_part(const void* __restrict__ x, int dtype, int64_t idx, int64_t count,
-                                               int valid) {
-  if (dtype != 0) return Raw8{load8_u16_part(static_cast<const uint16_t*>(x), idx, count, valid), uint4{0, 0, 0, 0}};
-  const uint32_t* p = static_cast<const uint32_t*>(x);
-  uint32_t w[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) w[e] = p[idx + e < count ? idx + e : count - 1];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) w[e] = e < valid ? w[e] : 0u;
-  return Raw8{uint4{w[0], w[1], w[2], w[3]}, uint4{w[4], w[5], w[6], w[7]}};
-}
-// 16-bit elements from `valid` on zeroed (the next row's, where a row ends
-// inside the eight).
-__device__ __forceinline__ uint4 keep_first(uint4 u, int valid) {
-  uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) w[e] = valid >= 2 * e + 2 ? w[e] : valid == 2 * e + 1 ? w[e] & 0xffffu : 0u;
-  return uint4{w[0], w[1], w[2], w[3]};
-}
-// Conversion of loaded elements by bit masks, one for each type: without
-// branches on the (uniform) type, which cost more than the conversions.
-struct TypeMask {
-  uint32_t f32, f16, bf16;
-  __device__ __forceinline__ explicit TypeMask(int dtype)
-      : f32(dtype == 0 ? ~0u : 0u), f16(dtype == 1 ? ~0u : 0u), bf16(dtype == 2 ? ~0u : 0u) {}
-  // element e of a row: w32 the dword it is in as fp32, w16 as a 16-bit type
-  __device__ __forceinline__ float value(uint32_t w32, uint32_t w16, int e) const {
-    const uint16_t h = (uint16_t)(w16 >> (16 * (e & 1)));
-    return __builtin_bit_cast(float, (w32 & f32) | (__builtin_bit_cast(uint32_t, F16::to_float(h)) & f16) |
-                                         (((uint32_t)h << 16) & bf16));
+// Sixteen bytes from element idx on (elements of 2^LG bytes, LG = 1 or 2) of an
+// array of `count` elements, zeros beyond its end, reading inside it only: the
+// array's last sixteen bytes where fewer are left, moved down by what they
+// start too early (one load; one by one, eight loads and their selects took
+// most of a step).
+template <int LG>
+__device__ __forceinline__ uint4 load16_end(const char* __restrict__ x, int64_t idx, int64_t count) {
+  constexpr int PER = 16 >> LG;
+  uint32_t w[4] = {0, 0, 0, 0};
+  if (count < PER) {
+    // a whole array of less than sixteen bytes
+    for (int e = 0; e < PER; ++e)
+      if (idx + e < count) {
+        if constexpr (LG == 1)
+          w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(x)[idx + e] << (16 * (e & 1));
+        else
+          w[e] = reinterpret_cast<const uint32_t*>(x)[idx + e];
+      }
+    return uint4{w[0], w[1], w[2], w[3]};
   }
-};
-// Eight elements as floats, those from `valid` on zero.
-__device__ __forceinline__ void raw8_floats(const Raw8& r, const TypeMask& tm, int valid, float (&f)[8]) {
-  const uint32_t a[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
+  const int64_t from = idx < count - PER ? idx : count - PER;
+  const int sh = (int)(idx - from < PER ? idx - from : PER);  // elements to drop
+  const uint4 u = load16(x + (from << LG));
+  w[0] = u.x;
+  w[1] = u.y;
+  w[2] = u.z;
+  w[3] = u.w;
+  const int d = sh >> (2 - LG);  // whole dwords
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    f[e] = tm.value(a[e], a[e >> 1], e);
-    f[e] = e < valid ? f[e] : 0.0f;
+  for (int bit = 2; bit > 0; bit >>= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = d & bit ? (e + bit < 4 ? w[e + bit < 4 ? e + bit : 3] : 0u) : w[e];
+  if constexpr (LG == 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = sh & 1 ? (w[e] >> 16) | (e < 3 ? w[e < 3 ? e + 1 : 3] << 16 : 0u) : w[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w[e] = sh >= PER ? 0u : w[e];
+  return uint4{w[0], w[1], w[2], w[3]};
+}
+__device__ __forceinline__ uint4 load8_u16_end(const uint16_t* __restrict__ x, int64_t idx, int64_t count) {
+  return load16_end<1>(reinterpret_cast<const char*>(x), idx, count);
+}
+__device__ __forceinline__ Raw8 load8_any_end(const void* __restrict__ x, int dtype, int64_t idx, int64_t count) {
+  const char* p = static_cast<const char*>(x);
+  if (dtype != 0) return Raw8{load16_end<1>(p, idx, count), uint4{0, 0, 0, 0}};
+  return Raw8{load16_end<2>(p, idx, count), load16_end<2>(p, idx + 4, count)};
+}
+// Masks of the first `valid` of eight 16-bit elements (the rest of a loaded
+// chunk belongs to the next row).  Kept in vector registers: as comparisons
+// they took a scalar register pair each, more than there are.
+__device__ __forceinline__ uint4 first_mask(int valid) {
+  uint32_t w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w[e] = valid >= 2 * e + 2 ? ~0u : valid == 2 * e + 1 ? 0xffffu : 0u;
+  return uint4{w[0], w[1], w[2], w[3]};
+}
+__device__ __forceinline__ uint4 and4(uint4 a, uint4 m) { return uint4{a.x & m.x, a.y & m.y, a.z & m.z, a.w & m.w}; }
+// Loaded elements as floats.  One (uniform) branch on the type for all of
+// them: a choice per element became a branch per element.
+template <int N>
+__device__ __forceinline__ void raw8_floats(const Raw8 (&r)[N], int dtype, float (&f)[N][8]) {
+  auto dw = [&](int i, int e) {
+    const uint32_t a[8] = {r[i].a.x, r[i].a.y, r[i].a.z, r[i].a.w, r[i].b.x, r[i].b.y, r[i].b.z, r[i].b.w};
+    return a[e];
+  };
+  if (dtype == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[i][e] = __builtin_bit_cast(float, dw(i, e));
+  } else if (dtype == 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[i][e] = F16::to_float((uint16_t)(dw(i, e >> 1) >> (16 * (e & 1))));
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[i][e] = BF16::to_float((uint16_t)(dw(i, e >> 1) >> (16 * (e & 1))));
   }
 }
 __device__ __forceinline__ void bf16_floats(uint4 u, float (&f)[8]) {
@@ -228,7 +261,11 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
   auto ccols = [&](int cc) { return C - 32 * cc - 8 * g; };
 
   const int ves = vdt == 0 ? 4 : 2, ges = gdt == 0 ? 4 : 2;
-  const TypeMask vtm(vdt), gtm(gdt);
+  uint4 km[DP], vm[NV];
+#pragma unroll
+  for (int dc = 0; dc < DP; ++dc) km[dc] = first_mask(dcols(dc));
+#pragma unroll
+  for (int cc = 0; cc < NV; ++cc) vm[cc] = first_mask(ccols(cc));
   // the steps before `full` can be loaded whole: every 16 bytes that fetch
   // reads lie inside the arrays
   auto whole = [&](int st) {
@@ -261,17 +298,15 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
   auto fetch_end = [&](int st) {
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
-      const int64_t r0 = (int64_t)st * kStep + 16 * kt, r = r0 + j;
+      const int64_t r0 = (int64_t)st * kStep + 16 * kt;
 #pragma unroll
-      for (int dc = 0; dc < DP; ++dc)
-        kn[kt][dc] = load8_u16_part(k, r * D + 32 * dc + 8 * g, N * D, r < N ? dcols(dc) : 0);
+      for (int dc = 0; dc < DP; ++dc) kn[kt][dc] = load8_u16_end(k, (r0 + j) * D + 32 * dc + 8 * g, N * D);
       if constexpr (ONE) {
-        const int64_t n = r0 + 4 * g;
-        v1n[kt] = load8_any_part(v, vdt, n, N, (int)(N - n < 4 ? N - n : 4)).a;
+        v1n[kt] = vdt == 0 ? load16_end<2>(static_cast<const char*>(v), r0 + 4 * g, N)
+                           : load16_end<1>(static_cast<const char*>(v), r0 + 4 * g, N);
       } else {
 #pragma unroll
-        for (int cc = 0; cc < CV; ++cc)
-          vn[kt][cc] = load8_any_part(v, vdt, r * C + 32 * cc + 8 * g, N * C, r < N ? ccols(cc) : 0);
+        for (int cc = 0; cc < CV; ++cc) vn[kt][cc] = load8_any_end(v, vdt, (r0 + j) * C + 32 * cc + 8 * g, N * C);
       }
     }
   };
@@ -285,11 +320,11 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
 #pragma unroll
     for (int dc = 0; dc < DP; ++dc) qreg[dc] = load8_u16(q, (q0 + j) * D + 32 * dc + 8 * g);
 #pragma unroll
-    for (int dc = 0; dc < DP; ++dc) qreg[dc] = keep_first(qreg[dc], dcols(dc));
+    for (int dc = 0; dc < DP; ++dc) qreg[dc] = and4(qreg[dc], km[dc]);
   } else {
 #pragma unroll
     for (int dc = 0; dc < DP; ++dc)
-      qreg[dc] = load8_u16_part(q, (q0 + j) * D + 32 * dc + 8 * g, M * D, q0 + j < M ? dcols(dc) : 0);
+      qreg[dc] = and4(load8_u16_end(q, (q0 + j) * D + 32 * dc + 8 * g, M * D), km[dc]);
   }
 #pragma unroll
   for (int dc = 0; dc < DP; ++dc) qq = square_sum<T>(qreg[dc], qq);
@@ -305,14 +340,16 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
 #pragma unroll
     for (int cc = 0; cc < CV; ++cc) {
       const int64_t idx = (q0 + j) * C + 32 * cc + 8 * g;
-      r[cc] = inside ? load8_any(gr, ges, idx) : load8_any_part(gr, gdt, idx, M * C, q0 + j < M ? ccols(cc) : 0);
+      r[cc] = inside ? load8_any(gr, ges, idx) : load8_any_end(gr, gdt, idx, M * C);
     }
+    raw8_floats(r, gdt, f);
 #pragma unroll
-    for (int cc = 0; cc < CV; ++cc) {
-      raw8_floats(r[cc], gtm, ccols(cc), f[cc]);
+    for (int cc = 0; cc < CV; ++cc)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) mb = umax32(mb, __builtin_bit_cast(uint32_t, fabsf(f[cc][e])));
-    }
+      for (int e = 0; e < 8; ++e) {
+        if (e >= ccols(cc)) f[cc][e] = 0.0f;
+        mb = umax32(mb, __builtin_bit_cast(uint32_t, fabsf(f[cc][e])));
+      }
     eg = scale_exponent(wave_umax(mb));
     const float sg = ldexpf(1.0f, eg);
 #pragma unroll
@@ -342,15 +379,22 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
-      for (int dc = 0; dc < DP; ++dc) kr[kt][dc] = keep_first(kn[kt][dc], dcols(dc));
+      for (int dc = 0; dc < DP; ++dc) kr[kt][dc] = and4(kn[kt][dc], km[dc]);
       if constexpr (ONE) {
-        const uint32_t u[4] = {v1n[kt].x, v1n[kt].y, v1n[kt].z, v1n[kt].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v1[kt][e] = vtm.value(u[e], u[e >> 1], e);
+        vr[kt][0] = Raw8{v1n[kt], v1n[kt]};
       } else {
 #pragma unroll
         for (int cc = 0; cc < CV; ++cc) vr[kt][cc] = vn[kt][cc];
       }
+    }
+    if constexpr (ONE) {
+      float f[2][8];
+      const Raw8 r1[2] = {vr[0][0], vr[1][0]};
+      raw8_floats(r1, vdt, f);
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v1[kt][e] = f[kt][e];
     }
     if (st + W < full) fetch(st + W);
 
@@ -375,9 +419,14 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
         for (int e = 0; e < 4; ++e) rs = fmaf(exp2_clamped(fmaf(sc[kt][e], tau2, bq)), v1[kt][e], rs);
       continue;
     }
-    // values: a larger magnitude than any before moves the scale (exact)
+    // values: a larger magnitude than any before moves the scale (exact).  What
+    // lies beyond a row's end is elements of other rows, masked after packing.
     float vf[2][NV][8];
     float vmax = 0.0f;
+    if constexpr (!ONE) {
+      raw8_floats(vr[0], vdt, vf[0]);
+      raw8_floats(vr[1], vdt, vf[1]);
+    }
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
       if constexpr (ONE) {
@@ -386,7 +435,6 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
       } else {
 #pragma unroll
         for (int cc = 0; cc < CV; ++cc) {
-          raw8_floats(vr[kt][cc], vtm, ccols(cc), vf[kt][cc]);
 #pragma unroll
           for (int e = 0; e < 8; ++e) vmax = fmaxf(vmax, fabsf(vf[kt][cc][e]));
         }
@@ -412,7 +460,7 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int cc = 0; cc < CV; ++cc) {
-          vh[kt][cc] = scaled_f16(vf[kt][cc], sv);
+          vh[kt][cc] = and4(scaled_f16(vf[kt][cc], sv), vm[cc]);
           *reinterpret_cast<uint4*>(vl + (kt * CV + cc) * 1024 + lrow) = vh[kt][cc];
         }
     }
