@@ -5,8 +5,11 @@ calibration kernels the benchmark measures the device's own rates with).
 Flags: -O3 for gfx950 only; packed fp32 instructions are disabled in the
 device code (-Xclang -target-feature -Xclang -packed-fp32-ops).
 """
+import concurrent.futures
 import os
+import re
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -31,12 +34,31 @@ def build(verbose: bool = False) -> str:
     """Compile csrc/gauss_sum.hip into libgauss_sum.so and peaks/gs_peaks.hip
     into libgs_peaks.so; returns the path of libgauss_sum.so."""
     compile_one(PEAKS_SRC, PEAKS_LIB, verbose)
-    return compile_one(SRC, LIB, verbose)
+    return compile_parts(SRC, LIB, verbose)
 
 
-def compile_one(src: str, lib: str, verbose: bool) -> str:
-    tmp = lib + ".tmp%d" % os.getpid()
-    cmd = [HIPCC] + FLAGS + ["-o", tmp, src]
+def compile_parts(src: str, lib: str, verbose: bool) -> str:
+    """Compile the parts of ``src`` (GS_PART = 0 .. GS_PARTS of the source) in
+    parallel, at most eight at a time, and link them into ``lib``."""
+    with open(src) as f:
+        last = int(re.search(r"#define GS_PARTS (\d+)", f.read()).group(1))
+    flags = [x for x in FLAGS if x != "-shared"]
+    with tempfile.TemporaryDirectory() as tmp:
+        def one(i):
+            obj = os.path.join(tmp, "part%d.o" % i)
+            run([HIPCC] + flags + ["-DGS_PART=%d" % i, "-c", "-o", obj, src], verbose)
+            return obj
+
+        workers = min(8, int(os.environ.get("MAX_JOBS", 0)) or os.cpu_count() or 1)
+        with concurrent.futures.ThreadPoolExecutor(workers) as pool:
+            objs = list(pool.map(one, range(last + 1)))
+        out = lib + ".tmp%d" % os.getpid()
+        run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + objs, verbose)
+    os.replace(out, lib)
+    return lib
+
+
+def run(cmd, verbose: bool) -> None:
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "not a recognized feature for this target"
     msgs = "\n".join(ln for ln in (res.stdout + res.stderr).splitlines() if noise not in ln)
@@ -44,6 +66,11 @@ def compile_one(src: str, lib: str, verbose: bool) -> str:
         raise RuntimeError("hipcc failed (%d):\n%s" % (res.returncode, msgs))
     if verbose and msgs.strip():
         print(msgs)
+
+
+def compile_one(src: str, lib: str, verbose: bool) -> str:
+    tmp = lib + ".tmp%d" % os.getpid()
+    run([HIPCC] + FLAGS + ["-o", tmp, src], verbose)
     os.replace(tmp, lib)
     return lib
 

@@ -879,8 +879,19 @@ __global__ __launch_bounds__(kWave * WPB) void k_fwd(
 // epilogue writes out = sum_n Phi score_n - tau sum_n Phi (k_n - q_m) (the
 // forward sum minus the query gradient with unit weights), or its split
 // partial.
+//
+// At D <= 32 the instances need about 125 (single channel) and 165 registers,
+// a few above or below a wave boundary from build to build: the hint asks for
+// four and three waves per SIMD there (M = N = 32768, D = 32, C = 4, 32 clusters,
+// sum and gradients 709 -> 641 us in one such build), as it does for the
+// several-channel pass at 32 < D <= 64, C <= 32 without a fused sum.
+constexpr int dq_waves(int DP, int CW, int FCT, bool SV) {
+  if (SV) return 2;
+  if (DP == 1) return CW == 0 ? 4 : CW == 1 ? 3 : 2;
+  return DP == 2 && CW == 1 && FCT == 0 ? 4 : 2;
+}
 template <typename T, int DP, int CW, int QT, int FCT, bool BZ, int WPB, bool SV = false>
-__global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(2))) void k_dq(
+__global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(dq_waves(DP, CW, FCT, SV)))) void k_dq(
     const uint4* __restrict__ qs, const float* __restrict__ nhq, const uint4* __restrict__ samp_rt,
     const float* __restrict__ samp_nh, const uint4* __restrict__ ks, const float* __restrict__ scal,
     const uint4* __restrict__ kt_ks, const uint32_t* __restrict__ kslot, const uint4* __restrict__ vs,

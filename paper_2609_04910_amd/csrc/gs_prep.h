@@ -24,11 +24,13 @@
 
 namespace gs {
 
+#if !defined(GS_PART) || GS_PART == 0  // (kernels that are no templates: in one build part only)
 __global__ void k_fill_f32(float* __restrict__ p, int64_t n, float val) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (; i < n; i += stride) p[i] = val;
 }
+#endif
 
 // ---------------------------------------------------------------- maxima
 
@@ -108,6 +110,7 @@ struct MaxArgs {
 // Partial maxima: workgroup (b, i) of grid (blocks, arrays) reduces its share
 // of array i into part[i * pitch + b].  No atomics, so nothing has
 // to be cleared first.
+#if !defined(GS_PART) || GS_PART == 0  // (kernels that are no templates: in one build part only)
 __global__ __launch_bounds__(kMaxBlock) void k_prep_max(MaxArgs a, uint32_t* __restrict__ part, int pitch, Bz bz) {
   __shared__ uint32_t wmax[kMaxBlock / kWave];
   const MaxSource s = a.src[blockIdx.y];
@@ -123,6 +126,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_prep_max(MaxArgs a, uint32_t* __r
     if (threadIdx.x == 0) part[blockIdx.y * pitch + blockIdx.x] = mb;
   }
 }
+#endif
 
 // ---------------------------------------------------------------- points
 
@@ -566,6 +570,7 @@ __device__ __forceinline__ void block_tree_sum(double acc, double* red, int thre
 }
 
 constexpr int kDotThreads = 1024;
+#if !defined(GS_PART) || GS_PART == 0  // (kernels that are no templates: in one build part only)
 __global__ __launch_bounds__(kDotThreads) void k_dot(const void* __restrict__ v, int dtype, const float* __restrict__ s,
                                                      int64_t n, double* __restrict__ out) {
   __shared__ double red[kDotThreads];
@@ -583,6 +588,7 @@ __global__ __launch_bounds__(256) void k_dot_final(const double* __restrict__ pa
   __shared__ double red[256];
   block_tree_sum((int)threadIdx.x < parts ? part[threadIdx.x] : 0.0, red, 256, out);
 }
+#endif
 
 // Split partials of one output: out[i] = sum_s part[s, i] in split order.
 struct CombineSeg {
@@ -642,11 +648,13 @@ __device__ __forceinline__ void combine_seg(const float* __restrict__ part, floa
 // The split partials of a pass's one or two outputs (a gradient and the
 // forward sum it carries) in one launch: workgroups below blocks0 take the
 // first.
+#if !defined(GS_PART) || GS_PART == 0  // (kernels that are no templates: in one build part only)
 __global__ __launch_bounds__(256) void k_combine(CombineSeg a, CombineSeg b, unsigned blocks0, int splits, Bz bz) {
   const bool first = blockIdx.x < blocks0;
   const CombineSeg s = first ? a : b;
   combine_seg(zoff(s.part, bz.ws), zoff(s.out, s.bz), s.count, splits, first ? blockIdx.x : blockIdx.x - blocks0,
               first ? blocks0 : gridDim.x - blocks0);
 }
+#endif
 
 }  // namespace gs
