@@ -21,8 +21,8 @@
 // Nothing of size M x N is ever stored.
 //
 // Range: kernel values are fp16 numbers in [0, 1].  When every row maximum of
-// the wave's queries over a fixed sample of keys (64 keys; the forward also
-// 1024, via k_row_check) is at least 2^-8 the offset off_m is 0.  Otherwise
+// the wave's queries over a fixed sample of keys (64 keys, then 1024:
+// the forward via k_row_check, the gradient itself at D <= 128) is at least 2^-8 the offset off_m is 0.  Otherwise
 // the forward kernel rounds 2^15 Phi instead, the exponent still clamped at
 // <= 0 before the exact shift by 15 (so values are at most 2^15, inside the
 // fp16 range, and keep full relative precision down to Phi = 2^-29), as long
