@@ -21,8 +21,9 @@
 // Nothing of size M x N is ever stored.
 //
 // Range: kernel values are fp16 numbers in [0, 1].  When every row maximum of
-// the wave's queries over a fixed sample of keys (64 keys, then 1024:
-// the forward via k_row_check, the gradient itself at D <= 128) is at least 2^-8 the offset off_m is 0.  Otherwise
+// the wave's queries over a fixed sample of keys (64 keys, then 1024: the
+// forward via k_row_check, the gradient itself at D <= 128 with several
+// channels) is at least 2^-8 the offset off_m is 0.  Otherwise
 // the forward kernel rounds 2^15 Phi instead, the exponent still clamped at
 // <= 0 before the exact shift by 15 (so values are at most 2^15, inside the
 // fp16 range, and keep full relative precision down to Phi = 2^-29), as long
@@ -367,20 +368,30 @@ __device__ __forceinline__ int wave_shift_level(const uint32_t* __restrict__ shi
 // forward kernel.  Otherwise a second pass over the wave's own key range takes
 // the exact row maxima (identical MFMA inputs and order as the main loop).
 // M = N = 32768, D = 32, C = 4, 32 clusters, tau = 1, sum and gradients: 1049 ->
-// 655 us.  Not at D > 128 (SCAN = false: the second pass only): any more code
+// 655 us.  Not at D > 128 (FIRST = 1: the second pass only): any more code
 // here pushes spills into the key loop of the instance with a fused sum
-// (M = 2^15, N = 2^18, C = 16: 14.7 -> 32 ms).
-template <typename T, int DP, int QT, bool SCAN>
+// (M = 2^15, N = 2^18, C = 16: 14.7 -> 32 ms).  Nor with a single channel: the
+// key bias there holds log2 |v|, so the second pass finds the row's largest
+// Phi |v|, which is what its fp16 values must be relative to; the sample knows
+// Phi only (M = N = 8000, D = 32, 32 clusters with weights from 1 to 2^-24,
+// tau = 1: 2822 rows beyond the stated bound with the scan, 42 without).  At
+// D <= 128 the compiler is not told that there is one pass: knowing it, it
+// gives the key loop other registers (the same instructions; N = 65536, D = 64
+// flow 1057 -> 1148 us, B = 4, M = N = 32768, D = 32, C = 1 sum and gradients
+// 1486 -> 1510 us).
+template <typename T, int DP, int QT, int FIRST>
 __device__ __forceinline__ void sampled_or_exact_offsets(const uint4* __restrict__ samp_rt,
                                                       const float* __restrict__ samp_nh,
                                                       const uint4* __restrict__ ks, const float* __restrict__ scal,
                                                       const uint4 (&qreg)[QT][DP], int s_begin, int s_end,
                                                       int64_t q0, int64_t M, int j, int g, float tau2,
                                                       float (&bq)[QT], float (&off)[QT]) {
-  const uint4* keys = SCAN ? samp_rt : ks + (int64_t)s_begin * (2 * DP * 64);
-  const float* bias = SCAN ? samp_nh : scal + (int64_t)s_begin * kScalarFloats;
-  int stride = SCAN ? kStep : kScalarFloats, steps = SCAN ? kSampleRows / kStep : s_end - s_begin;
-  for (int pass = SCAN ? 0 : 1; pass < 2; ++pass) {
+  int first = FIRST;
+  if constexpr (FIRST == 1 && DP <= 4) asm volatile("" : "+s"(first));
+  const uint4* keys = first == 0 ? samp_rt : ks + (int64_t)s_begin * (2 * DP * 64);
+  const float* bias = first == 0 ? samp_nh : scal + (int64_t)s_begin * kScalarFloats;
+  int stride = first == 0 ? kStep : kScalarFloats, steps = first == 0 ? kSampleRows / kStep : s_end - s_begin;
+  for (int pass = first; pass < 2; ++pass) {
     float smax[QT];
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) smax[qt] = -__builtin_inff();
@@ -1005,7 +1016,8 @@ __global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(dq_
     off[qt] = 0.0f;
   }
   if (needs_shift<T, DP, QT>(samp_rt, samp_nh, qreg, bq, tau2, q0, M, j, g))
-    sampled_or_exact_offsets<T, DP, QT, DP <= 4>(samp_rt, samp_nh, ks, scal, qreg, s_begin, s_end, q0, M, j, g, tau2, bq, off);
+    sampled_or_exact_offsets<T, DP, QT, DP <= 4 && (CW > 0 || SV) ? 0 : 1>(samp_rt, samp_nh, ks, scal, qreg, s_begin,
+                                                                          s_end, q0, M, j, g, tau2, bq, off);
   if constexpr (CW > 0) settle(greg);
 
   floatx4 dQ[QT][DT];
