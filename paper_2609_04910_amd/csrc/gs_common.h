@@ -148,6 +148,16 @@ __device__ __forceinline__ int point_scale_exponent(uint32_t max_bits) {
   return scale_exponent(max_bits) + kPointScaleHeadroom;
 }
 
+// Further exponent of the RT value copies, the operands of w = <g, v> in the
+// gradient passes over CW 32-wide chunks of channels.  The products P = Phi w
+// are rounded to fp16, and with largest magnitudes in [1, 2) on both sides they
+// use only the lower part of its range: rows far from their keys' bulk, or
+// whose values are small against the largest, had subnormal products (32
+// clusters with values from 1 to 2^-12, M = N = 8000, D = 32, C = 4: errors of
+// 7.7e-3 of the sum of |terms|; with this 1.4e-4).  At most
+// 32 CW (2^(h+1))^2 = 2^15 in magnitude, inside fp16's range.
+constexpr int w_headroom(int CW) { return CW == 1 ? 4 : CW <= 4 ? 3 : 2; }
+
 // Per-problem byte strides of a launch over a batch of problems: problem
 // blockIdx.z finds each operand at its base + blockIdx.z * stride.  One
 // problem: all zero, gridDim.z = 1.

@@ -33,7 +33,8 @@
 // of every row is 1 and fp16 keeps full relative precision for all values
 // within 2^-14 of it).  The epilogue multiplies by 2^off_m (off_m = -15 for
 // the shifted rows).  Values and upstream gradients are pre-scaled by exact
-// powers of two (largest magnitude in [1, 2)), undone in the epilogue.
+// powers of two (largest magnitude in [1, 2), as operands of w w_headroom
+// binades higher), undone in the epilogue.
 #pragma once
 
 #include "gs_common.h"
@@ -1371,7 +1372,7 @@ __global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(dq_
     float f = tau * exp2f(off[qt]);
     int e;
     if constexpr (CW > 0) {
-      e = -scale_exponent(*vslot) - scale_exponent(*gslot);
+      e = -scale_exponent(*vslot) - scale_exponent(*gslot) - 2 * w_headroom(CW);
     } else {
       // single channel: w = g_m v_n with v_n 2^(ev-1) in the kernel values
       e = 1 - scale_exponent(*vslot);

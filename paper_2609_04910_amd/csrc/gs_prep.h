@@ -5,9 +5,9 @@
 //    fp64), the key scalars of the passes these points are the keys of, a
 //    sample of rows for the row bound, and optionally a KS-layout fp16 copy
 //    (operand of sum_n P_mn k_n).  fp32 points: two fp16 parts instead.
-//  * values: exact power-of-two scaling so the largest |value| lies in [1, 2),
-//    then fp16 copies in RT layout (contraction over C) and / or KS layout
-//    (contraction over keys).
+//  * values: exact power-of-two scaling so the largest |value| lies in [1, 2)
+//    (RT: w_headroom binades higher), then fp16 copies in RT layout
+//    (contraction over C) and / or KS layout (contraction over keys).
 //
 // A call's whole preparation is one launch (k_prep), or two when the maxima
 // that the scales come from take more than a workgroup's glance (k_prep_max
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs a, Bz bz) {
         break;
       }
       case kJobValuesRt: {
-        const float s = ldexpf(1.0f, scale_exponent(maximum(J.slot)));
+        const float s = ldexpf(1.0f, scale_exponent(maximum(J.slot)) + w_headroom(1 << (J.lg - 2)));
         for (int64_t t = t0; t < J.items; t += stride)
           values_rt_item(src, J.dtype, J.n, J.width, 8 << J.lg, s, out, t >> J.lg, (int)(t & mask));
         break;

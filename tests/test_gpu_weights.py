@@ -111,3 +111,26 @@ def test_few_rows_beyond_the_bound_at_wide_weights():
         over = (np.abs(got[p] - ref) > parity.TOL["f16"] * scale).any(1)
         print(p, int(over.sum()), flush=True)
         assert over.mean() < 0.05
+
+
+@pytest.mark.parametrize("D,C,tau,qk", [(32, 4, 1.0, "f16"), (32, 4, 1.0, "bf16"), (32, 32, 1.0, "f16"),
+                                        (64, 20, 0.5, "f16"), (48, 60, 0.7, "f16"), (100, 40, 0.3, "bf16"),
+                                        (100, 128, 0.3, "f16"), (40, 256, 0.8, "f16")])
+def test_cluster_weights_several_channels(D, C, tau, qk):
+    # values fall to 2^-12 of the largest: a row's products Phi <g, v> are then
+    # small against the largest possible one whatever its Phi are
+    print(parity.check_workload(cluster_weights(D, C, 12, M=500, tau=tau, qk=qk)), flush=True)
+
+
+@pytest.mark.parametrize("C", [2, 32, 33, 64, 65, 128, 129, 256])
+def test_largest_products(C):
+    # every value and upstream gradient at the largest magnitude, kernel values
+    # next to 1: the products are as large as the scales allow
+    w = parity.random_workload(C, 600, 13000, 40, C, spread=1e-2)
+    w.v = np.full((13000, C), 1.9990234375, np.float16)
+    w.g = np.full((600, C), -3.998046875, np.float16)
+    got = parity.run(w, ("dq", "dk"))
+    for p in ("dq", "dk"):
+        rows = np.arange(0, 600 if p == "dq" else 13000, 41)
+        ref, scale = parity.oracle_ref(w, p, rows=rows)
+        print(parity.compare("%s C=%d" % (p, C), got[p][rows], ref, scale, parity.TOL["f16"]), flush=True)
