@@ -127,13 +127,19 @@ __device__ __forceinline__ float load_any(const void* p, int64_t i, int dtype) {
   return dtype == 1 ? F16::to_float(b) : BF16::to_float(b);
 }
 
-// Power-of-two scale exponent e with max * 2^e in [1, 2); 0 for max = 0, Inf or NaN.
+// Largest exponent of a scale: 2^e is applied as a factor, so it has to be
+// finite (arrays, key steps or rows of subnormal numbers only would ask for up
+// to 2^149, and a zero among them would become NaN).
+constexpr int kMaxScale = 126;
+
+// Power-of-two scale exponent e with max * 2^e in [1, 2), or less where e is at
+// its largest; 0 for max = 0, Inf or NaN.
 __device__ __forceinline__ int scale_exponent(uint32_t max_bits) {
   float mx = __builtin_bit_cast(float, max_bits);
   if (!(mx > 0.0f) || !(mx < __builtin_inff())) return 0;
   int e;
   (void)frexpf(mx, &e);  // mx = f * 2^e, f in [0.5, 1)
-  return 1 - e;
+  return 1 - e < kMaxScale ? 1 - e : kMaxScale;
 }
 
 // Exponent of the scale of the fp16 KS copy of bf16 points (the operand of
@@ -145,7 +151,8 @@ __device__ __forceinline__ int scale_exponent(uint32_t max_bits) {
 // its leading bits.
 constexpr int kPointScaleHeadroom = 14;
 __device__ __forceinline__ int point_scale_exponent(uint32_t max_bits) {
-  return scale_exponent(max_bits) + kPointScaleHeadroom;
+  const int e = scale_exponent(max_bits) + kPointScaleHeadroom;
+  return e < kMaxScale ? e : kMaxScale;
 }
 
 // Further exponent of the RT value copies, the operands of w = <g, v> in the
@@ -157,6 +164,10 @@ __device__ __forceinline__ int point_scale_exponent(uint32_t max_bits) {
 // 7.7e-3 of the sum of |terms|; with this 1.4e-4).  At most
 // 32 CW (2^(h+1))^2 = 2^15 in magnitude, inside fp16's range.
 constexpr int w_headroom(int CW) { return CW == 1 ? 4 : CW <= 4 ? 3 : 2; }
+__device__ __forceinline__ int w_scale_exponent(uint32_t max_bits, int CW) {
+  const int e = scale_exponent(max_bits) + w_headroom(CW);
+  return e < kMaxScale ? e : kMaxScale;
+}
 
 // Per-problem byte strides of a launch over a batch of problems: problem
 // blockIdx.z finds each operand at its base + blockIdx.z * stride.  One

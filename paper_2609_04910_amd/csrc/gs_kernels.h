@@ -1372,7 +1372,7 @@ __global__ __launch_bounds__(kWave * WPB) __attribute__((amdgpu_waves_per_eu(dq_
     float f = tau * exp2f(off[qt]);
     int e;
     if constexpr (CW > 0) {
-      e = -scale_exponent(*vslot) - scale_exponent(*gslot) - 2 * w_headroom(CW);
+      e = -w_scale_exponent(*vslot, CW) - w_scale_exponent(*gslot, CW);
     } else {
       // single channel: w = g_m v_n with v_n 2^(ev-1) in the kernel values
       e = 1 - scale_exponent(*vslot);

@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs a, Bz bz) {
         break;
       }
       case kJobValuesRt: {
-        const float s = ldexpf(1.0f, scale_exponent(maximum(J.slot)) + w_headroom(1 << (J.lg - 2)));
+        const float s = ldexpf(1.0f, w_scale_exponent(maximum(J.slot), 1 << (J.lg - 2)));
         for (int64_t t = t0; t < J.items; t += stride)
           values_rt_item(src, J.dtype, J.n, J.width, 8 << J.lg, s, out, t >> J.lg, (int)(t & mask));
         break;

@@ -364,7 +364,8 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
   }
 
   // running scales (powers of two) of the fp16 values and of the fp16 copy of
-  // bf16 keys: the exponent and the largest magnitude it is good for
+  // bf16 keys: the exponent and the largest magnitude it is good for (they come
+  // from single key steps, which may hold subnormal numbers only: kMaxScale)
   int ev = 0, ek = 0;
   float vlim = 0.0f, klim = 0.0f, sv = 1.0f, sk = 1.0f;
 

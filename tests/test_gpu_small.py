@@ -71,3 +71,49 @@ def test_small_batch_equals_single_calls():
         one = gs.gauss_sum_fwd_bwd(q[b], k[b], v[b], 0.05, g[b])
         for x, y in zip(out, one):
             assert torch.equal(x[b], y)
+
+
+def _bf16(x):
+    return wl._store_points(x.astype(np.float32), "bf16")
+
+
+@pytest.mark.parametrize("C", [1, 3, 40])
+@pytest.mark.parametrize("what", ["v", "v_most", "dout", "keys", "queries"])
+def test_blocks_of_tiny_numbers(what, C):
+    # scales come from single key steps and from 16 rows: steps and rows of
+    # subnormal (or, for bf16 points, nearly subnormal) numbers with zeros among
+    # them, beside ordinary ones
+    w = parity.random_workload(5, 300, 1000, 8, C, qk="bf16" if what in ("keys", "queries") else "f16", tau=0.3)
+    if what in ("v", "v_most"):
+        w.v[:64 if what == "v" else 700] *= np.float32(1e-39)
+        w.v[5:9] = 0.0
+    elif what == "dout":
+        w.g[16:48] *= np.float32(1e-39)
+        w.g[20] = 0.0
+    elif what == "keys":
+        kv = w.k_values.copy()
+        kv[:300] *= np.float32(1e-36)
+        w.k, w.k_values = _bf16(kv)
+    else:
+        qv = w.q_values.copy()
+        qv[:100] *= np.float32(1e-38)
+        w.q, w.q_values = _bf16(qv)
+    print(parity.check_workload(w), flush=True)
+
+
+@pytest.mark.parametrize("N", [1000, 13000])
+@pytest.mark.parametrize("C", [1, 3, 70])
+def test_subnormal_arrays(C, N):
+    # nothing but subnormal values, through the small and the prepared path:
+    # sums stay finite and, with upstream gradients of 2^100, the gradients are
+    # ordinary numbers (twice the usual bound: the values' own 2^-20, the copies'
+    # fp16 numbers near 2^-3 and fp32 sums near 2^-126 round a little more)
+    w = parity.random_workload(6, 200, N, 8, C, tau=0.3)
+    w.v = (np.sign(w.v) * (1.0 + np.abs(w.v)) * 1e-39).astype(np.float32)
+    w.g = np.sign(w.g) * np.float32(2.0 ** 100)
+    for fused in (False, True):
+        got = parity.run(w, ("fwd", "dq", "dk", "dv"), fused=fused)
+        assert np.all(np.isfinite(got["fwd"]))
+        for p in ("dq", "dk", "dv"):
+            ref, scale = parity.oracle_ref(w, p)
+            print(parity.compare("%s fused=%s" % (p, fused), got[p], ref, scale, 4e-3), flush=True)
