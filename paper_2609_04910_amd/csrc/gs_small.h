@@ -52,6 +52,7 @@ namespace gs {
 // than 4 C <= 2^8 for the at most 64 channels here, after scaling) below
 // fp16's largest number.
 constexpr float kSmallRaise = 6.0f;
+constexpr float kSmallCap = 64.0f;  // 2^kSmallRaise
 
 enum SmallKind : int {
   kSmallFwd,    // s
@@ -378,8 +379,10 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
 #pragma unroll
   for (int t = 0; t < NTA; ++t) acc[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
   // off: whole numbers (-3e38 before any exponent above -inf); cap: kernel
-  // value 1 relative to the offset
-  float rs = 0.0f, off = -3.0e38f, cap = __builtin_inff();
+  // value 1 relative to the offset, and no more than a raise leaves (where an
+  // exponent's terms are so large that they round by whole units, 2^27 and up,
+  // an exponent may come out above the offset taken from it)
+  float rs = 0.0f, off = -3.0e38f, cap = kSmallCap;
   const int src = 16 * (j >> 2) + (j & 3);  // a lane that holds key j's single-channel value
 
   for (; st < steps; st += W) {
@@ -541,6 +544,7 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
       rs *= f;
       off = nw;
       cap = exp2f(-nw);
+      if constexpr (!LOGV) cap = fminf(cap, kSmallCap);
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -554,7 +558,7 @@ __global__ __launch_bounds__(kWave * small_waves(DP, CV, KIND)) void k_small(Sma
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         phi[kt][e] = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(y[kt][e]), 0.0f,
-                                             LOGV ? fabsf(v1[kt][e]) * cap : cap);
+                                             LOGV ? fminf(fabsf(v1[kt][e]) * cap, kSmallCap) : cap);
       if constexpr (KIND == kSmallGrad) {
         if constexpr (ONE) {
 #pragma unroll

@@ -117,3 +117,23 @@ def test_subnormal_arrays(C, N):
         for p in ("dq", "dk", "dv"):
             ref, scale = parity.oracle_ref(w, p)
             print(parity.compare("%s fused=%s" % (p, fused), got[p], ref, scale, 4e-3), flush=True)
+
+
+@pytest.mark.parametrize("qk", ["f16", "bf16"])
+@pytest.mark.parametrize("C", [1, 3, 40])
+@pytest.mark.parametrize("size", [2e8, 8e9, 1e12])
+def test_far_from_the_origin_stays_finite(size, C, qk):
+    # tau |x|^2 far beyond the stated domain: exponents round by whole units and
+    # more, so results mean nothing, but no fp16 number may overflow
+    w = parity.random_workload(3, 200, 1000, 8, C, tau=size / 4e4)
+    q, k = w.q_values.astype(np.float32), w.k_values.astype(np.float32)
+    q[:, 0] += 200.0
+    k[:, 0] += 200.0
+    w.q, w.q_values = wl._store_points(q, qk)
+    w.k, w.k_values = wl._store_points(k, qk)
+    got = parity.run(w, ("fwd", "dq", "dk", "dv"), fused=True)
+    for p in ("fwd", "dq", "dk", "dv"):
+        assert np.all(np.isfinite(got[p])), p
+    import torch
+    phi = gs.gauss_sum_svgd(parity.to_torch(w.k), parity.to_torch(np.repeat(w.v[:, :1], 8, 1)), float(w.tau))
+    assert torch.isfinite(phi).all()
