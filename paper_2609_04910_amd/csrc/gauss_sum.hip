@@ -34,6 +34,7 @@ constexpr int kMaxStepsPerSplit = 1 << 17;
 constexpr int64_t kMaxRows = int64_t(1) << 30;
 constexpr int kSlotWords = 64;           // words of a plan's slots (one alignment unit)
 constexpr int kDefaultSlots = 512;       // resident workgroups assumed when no device can be queried
+constexpr size_t kScratchBytes = GAUSS_SUM_NOALLOC_SCRATCH_BYTES;  // scratch of gauss_sum_fwd_noalloc
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
@@ -532,6 +533,7 @@ struct Plan {
   float* scal_qg = nullptr;    // per-step scalars, keys q with values dout
   float* part = nullptr;       // split partials of the running pass
   float* part_s = nullptr;     // split partials of a forward sum fused into the dq pass
+  int64_t most = 0;            // pass_shape's bound on the splits of the forward pass
   size_t total = 0;
 };
 
@@ -570,9 +572,12 @@ int device_slots(const void* kernel, int threads) {
 // parts (partial sums combined afterwards): the split count that minimises
 // (rounds of resident workgroups) x (steps per split + fixed cost), searched
 // from the smallest count that fills the device once up to four times that.
-// `group` problems run side by side on grid.z.
+// `group` problems run side by side on grid.z.  most > 0: the split count for
+// which the plan fits the scratch array of gauss_sum_fwd_noalloc (see
+// splits_in_scratch), taken instead of a larger one if it is at least half of
+// what fills the device.
 PassShape pass_shape(int64_t rows, int64_t keys, int QT, const void* kernel, int64_t group,
-                     int wpb = kWavesPerBlock) {
+                     int wpb = kWavesPerBlock, int64_t most = 0) {
   PassShape ps;
   ps.blocks = (int)ceil_div(rows, 16 * QT * wpb);
   ps.steps = (int)ceil_div(keys, kStep);
@@ -594,6 +599,7 @@ PassShape pass_shape(int64_t rows, int64_t keys, int QT, const void* kernel, int
       splits = sp;
     }
   }
+  if (most > 0 && splits > most && most >= std::max<int64_t>(need, ceil_div(lo, 2))) splits = (int)most;
   ps.sps = (int)ceil_div(ps.steps, splits);
   ps.splits = ps.steps ? (int)ceil_div(ps.steps, ps.sps) : 1;
   return ps;
@@ -639,6 +645,20 @@ DqK dq_for(const gs_problem& p, const Dims& dm, bool fused) {
 const void* fwd_kernel(const gs_problem& p, const Dims& dm) { return fwd_for(p, dm).kernel; }
 const void* dq_kernel(const gs_problem& p, const Dims& dm, bool fused) { return dq_for(p, dm, fused).kernel; }
 
+// Splits of a forward pass whose partials (M x C floats each) still fit
+// gauss_sum_fwd_noalloc's scratch array beside the `base` bytes of the other
+// buffers (of the plan with separate points).  Only for the passes that split
+// finely: many short workgroups per row block at D <= 32, and the fp32 tier
+// with several channels, whose plans would otherwise outgrow the array by
+// partials alone (M = 745959, N = 164543, D = 8, C = 21: 74 MiB of copies and
+// four splits of 60 MiB).
+int64_t splits_in_scratch(const gs_problem& p, const Dims& dm, size_t base) {
+  const bool fine = p.qk_dtype == GS_F32 ? p.C > 1 : dm.DP == 1 && dm.CT <= 2;
+  if (!fine || base > kScratchBytes) return 0;
+  // (one split has no partials)
+  return std::max<int64_t>(1, (int64_t)((kScratchBytes - base) / ((size_t)p.M * p.C * 4)));
+}
+
 // Lays out every buffer the requested passes need for one problem of a group
 // of G; with ws == nullptr only computes the size.
 void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& pl, int64_t G) {
@@ -669,7 +689,12 @@ void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& p
       pl.v.ks = cv.take<uint16_t>(pl.Np * Rv * 2);  // high parts
       pl.v.rt = cv.take<uint16_t>(pl.Np * Rv * 2);  // low parts (same KS layout)
     }
-    const PassShape ps = pass_shape(p.M, p.N, f32_pass_qt(p.C, pl.dm.DP), f32_pass_kernel(p.C, pl.dm.DP), G);
+    if (G == 1) {
+      const size_t side = round_up(pl.Np * W * 2, kAlign) * 2 + round_up(pl.Np * 4, kAlign);
+      pl.most = splits_in_scratch(p, pl.dm, cv.off + (alias ? side : 0));
+    }
+    const PassShape ps = pass_shape(p.M, p.N, f32_pass_qt(p.C, pl.dm.DP), f32_pass_kernel(p.C, pl.dm.DP), G,
+                                    kWavesPerBlock, pl.most);
     pl.part = ps.splits > 1 ? cv.take<float>((size_t)ps.splits * p.M * p.C * 4) : nullptr;
     pl.total = cv.off;
     return;
@@ -713,11 +738,16 @@ void make_plan(const gs_problem& p, const Want& w, bool alias, void* ws, Plan& p
   if (wc) pl.g.rt = cv.take<uint16_t>(pl.Mp * Wv * 2);
   if (w.dv && !(w.fused_kv() && p.C == 1)) pl.g.ks = cv.take<uint16_t>(pl.Mp * Rv * 2);
 
+  if (w.fwd && !w.dq && !w.dk && !w.dv && G == 1) {
+    const size_t side = round_up(pl.Np * W * 2, kAlign) + round_up(pl.Np * 4, kAlign);
+    pl.most = splits_in_scratch(p, pl.dm, cv.off + (alias ? side : 0));
+  }
+
   // Partial-sum buffer for split passes (reused by every pass in turn).
   size_t part = 0, part_s = 0;
   auto consider = [&](int64_t rows, int64_t keys, int QT, int64_t width, const void* kernel,
                       int wpb = kWavesPerBlock) {
-    PassShape ps = pass_shape(rows, keys, QT, kernel, G, wpb);
+    PassShape ps = pass_shape(rows, keys, QT, kernel, G, wpb, pl.most);
     if (ps.splits > 1) part = std::max(part, (size_t)ps.splits * rows * width * 4);
     return ps.splits;
   };
@@ -1032,7 +1062,7 @@ void pass_fwd(const Ctx& c, const Side& qs, int64_t nq, const Side& ks, int64_t 
   const gs_problem& p = *c.p;
   const Dims& dm = c.pl->dm;
   const FwdK fk = fwd_for(p, dm);
-  PassShape ps = pass_shape(nq, nk, fwd_qt(dm.DP, dm.CT), fk.kernel, c.pl->G, fwd_wpb(dm.DP));
+  PassShape ps = pass_shape(nq, nk, fwd_qt(dm.DP, dm.CT), fk.kernel, c.pl->G, fwd_wpb(dm.DP), c.pl->most);
   const bool split = ps.splits > 1;
   float* dst = split ? c.pl->part : out;
   Bz bz = bz_ws(c);
@@ -1114,7 +1144,7 @@ void run_f32(const Ctx& c, const void* q, int64_t qs, const void* k, int64_t ks,
     // several channels: launches of up to kF32MaxChannels channels each
     const int CT = f32c_ct(C);
     const F32cK fk = f32c_for(DP, CT);
-    const PassShape ps = pass_shape(M, N, f32c_qt(DP, CT), fk.kernel, pl.G);
+    const PassShape ps = pass_shape(M, N, f32c_qt(DP, CT), fk.kernel, pl.G, kWavesPerBlock, pl.most);
     const bool split = ps.splits > 1;
     Bz bk = bz_ws(c);
     bk.out = split ? c.slice : os;
@@ -1292,7 +1322,6 @@ namespace gs {
 // per GPU, held until the process ends).  Host code never uses the symbol
 // itself as an address: its device address on the current GPU comes from
 // hipGetSymbolAddress, once per device.
-constexpr size_t kScratchBytes = GAUSS_SUM_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace {

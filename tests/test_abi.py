@@ -314,6 +314,14 @@ def test_noalloc_validation_and_scratch_limit():
         assert need > gs.NOALLOC_SCRATCH_BYTES
         assert _noalloc(M, N, D, C) == 10
     assert gs.gauss_sum_fwd_workspace_size(8, 8, 4, 2) <= gs.NOALLOC_SCRATCH_BYTES
+    # plans that exceed the scratch by split partials alone take fewer splits:
+    # copies of 70 - 115 MiB and a partial of 1 - 60 MiB each
+    for M, N, D, C, qk, v in ((745959, 164543, 8, 21, gs.GS_BF16, gs.GS_F16),
+                              (1517714, 119889, 1, 1, gs.GS_F16, gs.GS_F32),
+                              (357284, 49354, 14, 27, gs.GS_F16, gs.GS_F16),
+                              (62664, 2396, 1, 182, gs.GS_F32, gs.GS_F16),
+                              (299397, 4972, 23, 86, gs.GS_F32, gs.GS_F16)):
+        assert gs.gauss_sum_fwd_workspace_size(M, N, D, C, qk, v) <= gs.NOALLOC_SCRATCH_BYTES
     hdr = open(os.path.join(ROOT, "include", "gauss_sum.h")).read()
     assert "#define GAUSS_SUM_NOALLOC_SCRATCH_BYTES ((size_t)128 << 20)" in hdr
     assert gs.NOALLOC_SCRATCH_BYTES == 128 << 20
