@@ -63,6 +63,20 @@ def run(w, passes, alias=True, g=None, fused=False):
     return {k_: t.cpu().numpy() for k_, t in res.items() if t is not None}
 
 
+SENTINEL = 0xA5
+
+
+def route(call, nbytes):
+    """Which kernels a call took: "small" if call(workspace) left its workspace
+    (nbytes) untouched, as the one-launch kernel does, else "prepared" (point
+    copies are written there first)."""
+    import torch
+    ws = torch.full((nbytes,), SENTINEL, dtype=torch.uint8, device="cuda")
+    call(ws)
+    torch.cuda.synchronize()
+    return "small" if bool((ws == SENTINEL).all()) else "prepared"
+
+
 def oracle_ref(w, pas, rows=None, g=None):
     g = w.g if g is None else g
     qv, kv = w.q_values, w.k_values
