@@ -21,21 +21,6 @@
 namespace gs {
 inline namespace tables {
 
-constexpr size_t kAlign = 256;
-constexpr int kMinStepsPerSplit = 4;     // 128 keys
-constexpr int kSplitOverheadSteps = 8;   // per-workgroup fixed cost (prologue, epilogue), in key steps
-// Most key steps one split may cover: every key-side stream moves at most
-// 16 KiB per step, and a split's part of a stream is addressed through one
-// buffer resource (32-bit byte count) with 32-bit step offsets.
-constexpr int kMaxStepsPerSplit = 1 << 17;
-// Largest M and N accepted: the main kernels launch one workgroup of 256
-// threads per 64 QT rows, and a grid's x extent in threads must stay below
-// 2^32 (QT >= 1).
-constexpr int64_t kMaxRows = int64_t(1) << 30;
-constexpr int kSlotWords = 64;           // words of a plan's slots (one alignment unit)
-constexpr int kDefaultSlots = 512;       // resident workgroups assumed when no device can be queried
-constexpr size_t kScratchBytes = GAUSS_SUM_NOALLOC_SCRATCH_BYTES;  // scratch of gauss_sum_fwd_noalloc
-
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
 
@@ -281,17 +266,6 @@ SvK sv_fn(int DP, int CT) {
   return {};
 }
 
-// fp32 tier (fp32 points, C = 1, forward): the kernel for D chunks DP.
-inline const void* f32_kernel(int DP) {
-  switch (DP) {
-    case 1: return reinterpret_cast<const void*>(&k_fwd32<1>);
-    case 2: return reinterpret_cast<const void*>(&k_fwd32<2>);
-    case 4: return reinterpret_cast<const void*>(&k_fwd32<4>);
-    case 8: return reinterpret_cast<const void*>(&k_fwd32<8>);
-  }
-  return nullptr;
-}
-
 // fp32 tier, several channels: channel tiles per launch (16 * CT channels)
 // and the launcher of k_fwd32c.
 inline int f32c_ct(int64_t C) {
@@ -331,22 +305,6 @@ F32cK f32c_by_ct(int CT) {
   }
   return {};
 }
-
-inline F32cK f32c_for(int DP, int CT) {
-  switch (DP) {
-    case 1: return f32c_by_ct<1>(CT);
-    case 2: return f32c_by_ct<2>(CT);
-    case 4: return f32c_by_ct<4>(CT);
-    case 8: return f32c_by_ct<8>(CT);
-  }
-  return {};
-}
-
-// The fp32-tier forward kernel for this shape and its queries per wave.
-inline const void* f32_pass_kernel(int64_t C, int DP) {
-  return C == 1 ? f32_kernel(DP) : f32c_for(DP, f32c_ct(C)).kernel;
-}
-inline int f32_pass_qt(int64_t C, int DP) { return C == 1 ? f32_qt(DP) : f32c_qt(DP, f32c_ct(C)); }
 
 // Small problems (k_small): instances for D <= 128 and the values' chunks.
 using SmFn = void (*)(dim3, hipStream_t, const SmallSide&, const SmallSide&, unsigned, float, float, int, int);
@@ -395,8 +353,10 @@ SmFn small_fn_t(int DP, int CV, int kind) {
 // ------------------------------------------------------------ build parts
 //
 // The kernels may be compiled as one translation unit (no GS_PART), or, in
-// parallel, as GS_PARTS units of this file: part 0 holds everything but the
-// tables below, part i only the i-th of them.  The parts also get the better
+// parallel, as GS_PARTS + 1 units of this file: part 0 holds everything but the
+// tables below, part i only the i-th of them (what names a kernel outside these
+// tables stands after them, in part 0: named here, in a function that is no
+// template, it would be compiled into every part).  The parts also get the better
 // code: as one unit the single-channel gradient at D <= 32 took 128 to 130
 // registers instead of 124, and B = 4, M = N = 32768, C = 1, sum and gradients
 // 1509 us instead of 1486.
@@ -496,6 +456,48 @@ template F32cK f32c_by_ct<8>(int);
 #if !defined(GS_PART) || GS_PART == 0
 namespace gs {
 namespace {
+
+constexpr size_t kAlign = 256;
+constexpr int kMinStepsPerSplit = 4;     // 128 keys
+constexpr int kSplitOverheadSteps = 8;   // per-workgroup fixed cost (prologue, epilogue), in key steps
+// Most key steps one split may cover: every key-side stream moves at most
+// 16 KiB per step, and a split's part of a stream is addressed through one
+// buffer resource (32-bit byte count) with 32-bit step offsets.
+constexpr int kMaxStepsPerSplit = 1 << 17;
+// Largest M and N accepted: the main kernels launch one workgroup of 256
+// threads per 64 QT rows, and a grid's x extent in threads must stay below
+// 2^32 (QT >= 1).
+constexpr int64_t kMaxRows = int64_t(1) << 30;
+constexpr int kSlotWords = 64;           // words of a plan's slots (one alignment unit)
+constexpr int kDefaultSlots = 512;       // resident workgroups assumed when no device can be queried
+constexpr size_t kScratchBytes = GAUSS_SUM_NOALLOC_SCRATCH_BYTES;  // scratch of gauss_sum_fwd_noalloc
+
+// fp32 tier (fp32 points, C = 1, forward): the kernel for D chunks DP.
+inline const void* f32_kernel(int DP) {
+  switch (DP) {
+    case 1: return reinterpret_cast<const void*>(&k_fwd32<1>);
+    case 2: return reinterpret_cast<const void*>(&k_fwd32<2>);
+    case 4: return reinterpret_cast<const void*>(&k_fwd32<4>);
+    case 8: return reinterpret_cast<const void*>(&k_fwd32<8>);
+  }
+  return nullptr;
+}
+
+inline F32cK f32c_for(int DP, int CT) {
+  switch (DP) {
+    case 1: return f32c_by_ct<1>(CT);
+    case 2: return f32c_by_ct<2>(CT);
+    case 4: return f32c_by_ct<4>(CT);
+    case 8: return f32c_by_ct<8>(CT);
+  }
+  return {};
+}
+
+// The fp32-tier forward kernel for this shape and its queries per wave.
+inline const void* f32_pass_kernel(int64_t C, int DP) {
+  return C == 1 ? f32_kernel(DP) : f32c_for(DP, f32c_ct(C)).kernel;
+}
+inline int f32_pass_qt(int64_t C, int DP) { return C == 1 ? f32_qt(DP) : f32c_qt(DP, f32c_ct(C)); }
 
 // ------------------------------------------------------------ workspace plan
 
