@@ -40,24 +40,37 @@ def gpu_inputs(w, alias=True):
     return q, k, v, g
 
 
-def run(w, passes, alias=True, g=None, fused=False):
+def run(w, passes, alias=True, g=None, fused=False, routes=None):
     """Runs the requested passes on the GPU (separate gauss_sum_fwd /
     gauss_sum_bwd calls, or one gauss_sum_fwd_bwd call when fused); returns
-    numpy fp32 results."""
+    numpy fp32 results.  routes: a list that takes each call's route (see
+    route)."""
     import torch
     q, k, v, gd = gpu_inputs(w, alias)
     if g is not None:
         gd = to_torch(g)
     res = {}
     want = tuple(p in passes for p in ("dq", "dk", "dv"))
+    dims = (w.M, w.N, w.D, w.C, gs._dtype_code(q.dtype), gs._dtype_code(v.dtype))
+
+    def call(fn, size):
+        out = []
+        if routes is None:
+            out.append(fn(None))
+        else:
+            routes.append(route(lambda ws: out.append(fn(ws)), size))
+        return out[0]
     if fused:
-        s, dq, dk, dv = gs.gauss_sum_fwd_bwd(q, k, v, float(w.tau), gd, want=want)
+        s, dq, dk, dv = call(lambda ws: gs.gauss_sum_fwd_bwd(q, k, v, float(w.tau), gd, want=want, workspace=ws),
+                             gs.gauss_sum_fwd_bwd_workspace_size(*dims, *want))
         res.update({"fwd": s, "dq": dq, "dk": dk, "dv": dv})
     else:
         if "fwd" in passes:
-            res["fwd"] = gs.gauss_sum_fwd(q, k, v, float(w.tau))
+            res["fwd"] = call(lambda ws: gs.gauss_sum_fwd(q, k, v, float(w.tau), workspace=ws),
+                              gs.gauss_sum_fwd_workspace_size(*dims))
         if any(want):
-            dq, dk, dv = gs.gauss_sum_bwd(q, k, v, float(w.tau), gd, want=want)
+            dq, dk, dv = call(lambda ws: gs.gauss_sum_bwd(q, k, v, float(w.tau), gd, want=want, workspace=ws),
+                              gs.gauss_sum_bwd_workspace_size(*dims, *want))
             res.update({"dq": dq, "dk": dk, "dv": dv})
     torch.cuda.synchronize()
     return {k_: t.cpu().numpy() for k_, t in res.items() if t is not None}
@@ -131,11 +144,12 @@ def compare(label, got, ref, scale, tol):
     return worst, rel_l2
 
 
-def check_workload(w, passes=None, rows=None, key_rows=None, alias=True, label=None, fused=None):
+def check_workload(w, passes=None, rows=None, key_rows=None, alias=True, label=None, fused=None, path=None):
     """Runs ``passes`` on the GPU and checks them against the oracle (all rows,
     or the given query rows / key rows).  With passes holding the forward and
     a gradient, both the separate calls and the fused gauss_sum_fwd_bwd call
     are checked (fused=None), or only one of them (fused=False / True).
+    path: the route every call has to take ("small" or "prepared").
     Returns a dict of (max err/A, rel-L2)."""
     passes = passes or w.passes
     label = label or w.name
@@ -143,7 +157,9 @@ def check_workload(w, passes=None, rows=None, key_rows=None, alias=True, label=N
     if w.g is None and grads:
         w.g = np.random.default_rng(99).standard_normal((w.M, w.C)).astype(np.float32)
     modes = [False, True] if fused is None and grads and "fwd" in passes else [bool(fused)]
-    results = [(f, run(w, passes, alias=alias, fused=f)) for f in modes]
+    routes = [] if path else None
+    results = [(f, run(w, passes, alias=alias, fused=f, routes=routes)) for f in modes]
+    assert not path or set(routes) == {path}, (label, routes)
     tol = TOL[w.qk_dtype]
     stats = {}
     for p in passes:

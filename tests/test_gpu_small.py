@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 1), (17, 31, 1, 1), (16, 257, 3, 1), (33, 1000, 32, 1), (100, 129, 33, 1), (65, 513, 100, 1),
     (15, 33, 7, 2), (40, 600, 31, 16), (64, 512, 64, 32), (50, 300, 65, 17), (30, 270, 128, 31),
     (70, 290, 5, 33), (35, 261, 40, 64), (19, 100, 97, 50),
-    (2048, 2048, 50, 1),        # at the limits of the dispatch
+    (2048, 2048, 50, 1),        # many workgroups (the dispatch's limits: below)
     (2049, 2100, 100, 1),
 ])
 def test_small_matches_oracle(M, N, D, C, qk):
@@ -137,3 +137,30 @@ def test_far_from_the_origin_stays_finite(size, C, qk):
     import torch
     phi = gs.gauss_sum_svgd(parity.to_torch(w.k), parity.to_torch(np.repeat(w.v[:, :1], 8, 1)), float(w.tau))
     assert torch.isfinite(phi).all()
+
+
+# The dispatch's limits: the longest chains of key steps that the kernel takes
+# and one step more, for sixteen and for eight waves, and the most rounds of
+# workgroups; both sides against the oracle.
+@pytest.mark.parametrize("M,N,D,C,want,path", [
+    (2048, 8192, 20, 1, "fwd", "small"),        # 256 steps: 16 a wave
+    (2048, 8193, 20, 1, "fwd", "prepared"),     # 17
+    (2100, 6656, 50, 1, "fwd", "small"),        # 13 of sixteen waves
+    (2100, 6657, 50, 1, "fwd", "prepared"),
+    (2100, 4864, 20, 20, "fwd", "small"),       # 152 steps: 19 of eight waves
+    (2100, 4865, 20, 20, "fwd", "prepared"),
+    (4096, 4096, 20, 1, "fwd", "small"),        # one round of 256 workgroups
+    (4112, 4096, 20, 1, "fwd", "prepared"),     # a second one
+    (2048, 2048, 100, 20, "fwd", "small"),      # 8192 tiles
+    (2048, 2049, 100, 20, "fwd", "prepared"),
+    (4096, 4096, 20, 1, "dq", "small"),
+    (4097, 4096, 20, 1, "dq", "prepared"),
+    (4000, 4096, 50, 1, "dq", "small"),
+])
+def test_limits_of_the_dispatch(M, N, D, C, want, path):
+    w = parity.random_workload(M + N, M, N, D, C)
+    rows, routes = np.arange(0, M, 29), []
+    got = parity.run(w, (want,), routes=routes)
+    assert routes == [path]
+    ref, scale = parity.oracle_ref(w, want, rows=rows)
+    print(parity.compare(want, got[want][rows], ref, scale, parity.TOL["f16"]), flush=True)
