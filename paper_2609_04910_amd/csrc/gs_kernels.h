@@ -376,10 +376,11 @@ __device__ __forceinline__ int wave_shift_level(const uint32_t* __restrict__ shi
 // Phi |v|, which is what its fp16 values must be relative to; the sample knows
 // Phi only (M = N = 8000, D = 32, 32 clusters with weights from 1 to 2^-24,
 // tau = 1: 2822 rows beyond the stated bound with the scan, 42 without).  At
-// D <= 128 the compiler is not told that there is one pass: knowing it, it
+// D <= 64 the compiler is not told that there is one pass: knowing it, it
 // gives the key loop other registers (the same instructions; N = 65536, D = 64
 // flow 1057 -> 1148 us, B = 4, M = N = 32768, D = 32, C = 1 sum and gradients
-// 1486 -> 1510 us).
+// 1486 -> 1510 us); at D = 65 - 128 it has to know it (M = 30001, N = 20003,
+// D = 100 620 -> 675 us otherwise).
 template <typename T, int DP, int QT, int FIRST>
 __device__ __forceinline__ void sampled_or_exact_offsets(const uint4* __restrict__ samp_rt,
                                                       const float* __restrict__ samp_nh,
@@ -388,7 +389,7 @@ __device__ __forceinline__ void sampled_or_exact_offsets(const uint4* __restrict
                                                       int64_t q0, int64_t M, int j, int g, float tau2,
                                                       float (&bq)[QT], float (&off)[QT]) {
   int first = FIRST;
-  if constexpr (FIRST == 1 && DP <= 4) asm volatile("" : "+s"(first));
+  if constexpr (FIRST == 1 && DP <= 2) asm volatile("" : "+s"(first));
   const uint4* keys = first == 0 ? samp_rt : ks + (int64_t)s_begin * (2 * DP * 64);
   const float* bias = first == 0 ? samp_nh : scal + (int64_t)s_begin * kScalarFloats;
   int stride = first == 0 ? kStep : kScalarFloats, steps = first == 0 ? kSampleRows / kStep : s_end - s_begin;
