@@ -845,11 +845,11 @@ constexpr int64_t kSmallSlots = 256;  // workgroups running at once (CUs)
 enum SmallLimit : int { kLimSum, kLimOne, kLimBoth, kLimSvgd };  // kLimOne / kLimBoth: one or both gradients
 // by point type (fp16, bf16), limit, D <= 32, 64, 128 and C = 1, <= 16, 32, 64
 constexpr uint8_t kSmallCost[2][4][3][4] = {
-    {{{19, 17, 22, 25}, {16, 17, 22, 22}, {15, 11, 13, 13}},
+    {{{19, 17, 22, 25}, {16, 23, 22, 22}, {15, 11, 13, 13}},
      {{11, 16, 16, 10}, {22, 19, 19, 10}, {18, 12, 12, 6}},
      {{28, 22, 35, 78}, {66, 49, 66, 78}, {36, 22, 36, 36}},
      {{0, 19, 19, 0}, {0, 0, 0, 13}, {0, 0, 0, 0}}},
-    {{{19, 17, 22, 25}, {16, 17, 22, 22}, {15, 11, 13, 13}},
+    {{{19, 17, 22, 25}, {16, 23, 22, 22}, {15, 11, 13, 13}},
      {{19, 16, 16, 10}, {22, 19, 19, 10}, {18, 8, 8, 6}},
      {{40, 22, 35, 78}, {66, 49, 66, 78}, {36, 22, 36, 36}},
      {{0, 19, 19, 0}, {0, 0, 0, 13}, {0, 0, 0, 0}}}};
