@@ -124,6 +124,8 @@ def dominant_kernel_name(workload):
     (the one whose traffic --traffic-from records)."""
     if workload == "batch_grad_d32":
         return "k_dq"
+    if workload == "dense_d16":
+        return "k_small"  # one launch computes the whole call
     if workload.startswith("batch_"):
         return "k_fwd32" if workload.endswith("_f32") else "k_fwd"
     return "k_dq" if any(p != "fwd" for p in PASSES[workload]) else "k_fwd"
@@ -528,12 +530,13 @@ def measure_workload(args, name, tau, steps, warmup, settle_ms, graph=False, flo
                           "frac": alg_flops / (ms_per_step * 1e-3) / PEAK_MFMA_F16},
         "roofline": {
             "bound": "mfma",
-            "kernel": ("k_dq (forward fused)" if (fused and fwd_in_dq) else "k_dq") if any(grads) else "k_fwd",
+            "kernel": ("k_dq (forward fused)" if (fused and fwd_in_dq) else "k_dq") if any(grads)
+                      else dominant_kernel_name(name),
             "achieved": achieved,
             "peak": PEAK_MFMA_F16 / 1e12,
             "unit": "TFLOP/s",
             "frac": achieved / (PEAK_MFMA_F16 / 1e12),
-            "traffic": recorded_traffic(name, "k_dq" if any(grads) else "k_fwd"),
+            "traffic": recorded_traffic(name, "k_dq" if any(grads) else dominant_kernel_name(name)),
             "avg_launch_ms": avg_kernel_ms,
             "std_launch_ms": float(np.std(kernel_ms)) if kernel_ms else float("nan"),
             "launches": len(kernel_ms),

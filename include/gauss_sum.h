@@ -52,6 +52,12 @@
  *     be centred on a common point by the caller first: Eq. 1 and its
  *     gradients are invariant under a common translation of q and k (the
  *     centring of Sec. 2, Remark 2).
+ *   - Unequal values: fp16 copies of v and dout (C > 1) keep their precision
+ *     down to 2^-14 of the largest of the call, and where a row's sampled keys
+ *     reach Phi = 2^-8 kernel values (C = 1: times |v|) are rounded relative to
+ *     the largest possible one.  Rows whose near keys all carry values below
+ *     about 2^-14 of the largest may exceed the bound there; small calls
+ *     (computed in one launch) do not for C = 1.
  */
 #ifndef GAUSS_SUM_H
 #define GAUSS_SUM_H

@@ -13,11 +13,12 @@
 // that the scales come from take more than a workgroup's glance (k_prep_max
 // first): the work is linear and short, so separate kernels (up to 17 of them
 // for a forward and full gradient, each a dependent launch of 3 - 5 us and as
-// much host time) cost small calls most of their time.  Per pass, before and
-// after: a flow of 1000 particles in D = 3 51 -> 28 us, an SVGD direction of
-// 1500 in D = 45 39 -> 26 us, sum and gradients through autograd at
-// M = 3001, N = 5003, D = 50, C = 10 265 -> 116 us, sum and gradients at
-// M = N = 16384, D = C = 128 720 -> 685 us.
+// much host time) cost ordinary calls much of their time.  Per call, before and
+// after (the smallest calls do not prepare at all: gs_small.h): a sum at
+// M = N = 9000, D = 16 47 -> 33 us, a flow of 6000 particles in D = 3 60 -> 35 us,
+// an SVGD direction of 4000 in D = 45 53 -> 42 us, sum and gradients through
+// autograd at M = 6001, N = 9003, D = 50, C = 10 214 - 262 -> 176 us, sum and
+// gradients at M = N = 16384, D = C = 128 722 -> 687 us.
 #pragma once
 
 #include "gs_common.h"
